@@ -51,6 +51,14 @@ __device__ __forceinline__ void buffer_store(float v, __amdgpu_buffer_rsrc_t r, 
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)voff, (int)soff, 0);
 }
 
+template <typename T>
+__device__ __forceinline__ T buffer_load(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+  if constexpr (sizeof(T) == 8)
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, 0, 0));
+  else
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, 0, 0));
+}
+
 // The few per-problem values the image and indexing helpers need, held in
 // registers by the kernels that use them.
 template <typename T>
@@ -138,6 +146,54 @@ __device__ __forceinline__ double ramp_at(const Geo<T> &g, int64_t c) {
 template <typename T>
 __device__ __forceinline__ double ramp_step(const Geo<T> &g, int j, int p) {
   return j == 0 ? (p ? g.ramp : -g.ramp) / (double)g.n[0] : 0.0;
+}
+
+// Broadcast of lane V of each row of 16 lanes (DPP row_newbcast) to the row: a
+// value that lane l holds for voxel l % 16 of a 4 x 4 tile reaches all 64
+// velocities as an operand, without an LDS read. The source register must not
+// be written by the two instructions before (callers put an s_nop behind the
+// last write).
+template <int V>
+__device__ __forceinline__ double bcast(double x) {
+  double r;
+  asm("v_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x), "n"(V));
+  return r;
+}
+template <int V>
+__device__ __forceinline__ float bcast(float x) {
+  float r;
+  asm("v_mov_b32_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x), "n"(V));
+  return r;
+}
+// acc = fma(x of lane V, y, acc)
+template <int V>
+__device__ __forceinline__ void fmac_bcast(double &acc, double x, double y) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(V));
+}
+template <int V>
+__device__ __forceinline__ void fmac_bcast(float &acc, float x, float y) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(V));
+}
+// (x of lane V) + y
+template <int V>
+__device__ __forceinline__ uint32_t add_bcast(uint32_t x, uint32_t y) {
+  uint32_t r;
+  asm("v_add_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x), "v"(y), "n"(V));
+  return r;
+}
+
+// A copy in a register of its own, made here: without it the compiler renames
+// the loaded value instead and moves the next load's result in its place at the
+// end of a loop, where that move waits for the load.
+__device__ __forceinline__ double reg_copy(double x) {
+  double r;
+  asm volatile("v_mov_b64 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+__device__ __forceinline__ float reg_copy(float x) {
+  float r;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(x));
+  return r;
 }
 
 constexpr uint32_t R_SKIP = 0x80000000u;  // solid voxel or outside the tile

@@ -561,8 +561,9 @@ Layout<T> make_layout(const Problem &P) {
   L.fidx = take((size_t)P.fluid * 4);
   L.scratch = take(8 * N * 8);  // tau, q (3), rho, u (3) staging
   // pipeline counters: at most one per (band, chain rounded up to 8) of the
-  // row pipeline or the strips
-  L.progress = take((size_t)(P.n[1] + 8) * (((P.ngroups << P.dim) + 7) / 8 * 8) * 4);
+  // row pipeline or the strips; the 4x4 row pipeline's padded
+  const size_t chains = (size_t)P.ngroups << P.dim, bands4 = ((size_t)P.ntile[1] + band_waves(4) - 1) / band_waves(4);
+  L.progress = take(std::max((size_t)(P.n[1] + 8) * ((chains + 7) / 8 * 8) * 4, bands4 * chains * kProgPad * 4));
   L.total = o;
   return L;
 }
@@ -663,6 +664,7 @@ struct pdvm_solver {
   char *scratch_dev = nullptr;
   hipError_t scratch_err = hipSuccess;
   size_t scr_part = 0, scr_prog = 0, scr_xcc = 0, scr_qctr = 0, scr_qflags = 0, scr_need = 0;
+  int scr_pad = 1;                 // ints per row-pipeline counter there
   std::vector<int64_t> start_iters;
   hipGraphExec_t graph = nullptr;
   int graph_iters = 0;
@@ -1355,8 +1357,10 @@ int create_common(const pdvm_config *cfgs, int n, void *dev_workspace, size_t ws
     const int rc2 = probe_xcd_locality(s, s->h_row_off, s->precision == PDVM_FP64 ? s->bd.row_stride
                                                                                   : s->bf.row_stride,
                                        P0.ngroups << P0.dim,
-                                       kWave * band_waves(s->precision == PDVM_FP64 ? s->bd.tile_edge
-                                                                                    : s->bf.tile_edge),
+                                       (s->precision == PDVM_FP64 ? uses_rows4(s->bd) : uses_rows4(s->bf))
+                                           ? rows4_threads()
+                                           : kWave * band_waves(s->precision == PDVM_FP64 ? s->bd.tile_edge
+                                                                                          : s->bf.tile_edge),
                                        &s->rows_local);
     if (rc2 != PDVM_OK) {
       g_thread_error = s->err;
@@ -1409,10 +1413,15 @@ int create_common(const pdvm_config *cfgs, int n, void *dev_workspace, size_t ws
     s->scr_part = 0;
     s->scr_prog = align256((size_t)s->h_blk_off[n] * 4 * sizeof(double));
     const size_t pipe = (size_t)std::max(s->h_row_off[n], s->h_strip_off[n]);
-    s->scr_xcc = s->scr_prog + align256(pipe * sizeof(int32_t));
-    s->scr_qctr = s->scr_xcc + align256(pipe);
-    s->scr_qflags = s->scr_qctr + (s->queue ? align256(kQueueCounterInts * 4) : 0);
-    s->scr_need = s->scr_qflags + (s->queue ? align256(s->qflag_ints * 4) : 0);
+    const bool rows4 = s->rows && (s->precision == PDVM_FP64 ? uses_rows4(s->bd) : uses_rows4(s->bf));
+    for (int pad : {rows4 ? kProgPad : 1, 1}) {  // padded counters where they fit
+      s->scr_pad = pad;
+      s->scr_xcc = s->scr_prog + align256(pipe * sizeof(int32_t) * pad);
+      s->scr_qctr = s->scr_xcc + align256(pipe);
+      s->scr_qflags = s->scr_qctr + (s->queue ? align256(kQueueCounterInts * 4) : 0);
+      s->scr_need = s->scr_qflags + (s->queue ? align256(s->qflag_ints * 4) : 0);
+      if (s->scr_need <= kNoAllocScratchBytes) break;
+    }
     s->start_iters.assign(n, 0);
   }
   *out = s;
@@ -1528,6 +1537,7 @@ int iterate_noalloc(pdvm_solver *s, int64_t max_iters, double tol, int32_t stop_
   Scratch scr;
   scr.part = (double *)(s->scratch_dev + s->scr_part);
   scr.progress = (int32_t *)(s->scratch_dev + s->scr_prog);
+  scr.prog_pad = s->scr_pad;
   scr.xcc = (uint8_t *)(s->scratch_dev + s->scr_xcc);
   if (s->queue) {
     scr.qctr = (int32_t *)(s->scratch_dev + s->scr_qctr);
@@ -1538,7 +1548,10 @@ int iterate_noalloc(pdvm_solver *s, int64_t max_iters, double tol, int32_t stop_
   // the counters hold whatever an earlier solve on this GPU left: set them
   // below every stamp of this call
   if (s->queue) HIPCHK(s, launch_fill_i32(scr.qflags, (int64_t)s->qflag_ints, 0, s->stream));
-  if (s->rows || s->strips) {
+  if (s->rows && (s->precision == PDVM_FP64 ? uses_rows4(s->bd) : uses_rows4(s->bf))) {
+    if (s->precision == PDVM_FP64) HIPCHK(s, launch_rows4_reset<double>(s->bd, scr, s->stream));
+    else HIPCHK(s, launch_rows4_reset<float>(s->bf, scr, s->stream));
+  } else if (s->rows || s->strips) {
     if (s->precision == PDVM_FP64)
       HIPCHK(s, launch_progress_reset<double>(s->bd, s->strips ? s->bd.d_strip_off : s->bd.d_row_off, s->strips,
                                               scr.progress, s->stream));

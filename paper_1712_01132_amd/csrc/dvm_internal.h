@@ -10,6 +10,9 @@ constexpr int kWave = 64;     // CDNA wavefront width: one discrete velocity per
 // Tile rows (one wavefront each) per block of the 2D row-pipeline sweep, by
 // compiled tile edge: the LDS ring between them fits twice in one CU's LDS.
 constexpr int band_waves(int tile_edge) { return tile_edge == 4 ? 8 : 4; }
+// The 4x4 row pipeline gives each progress counter a 128-byte line of its own
+// (problems' workspaces always; the static scratch where it has the room).
+constexpr int kProgPad = 32;
 constexpr int kRing = 64;     // permeability history kept at multiples of 100 iterations
 constexpr int kMomBlock = 256;
 constexpr int kSrcStride = 4; // per-voxel source record: nu rho, 2 nu u_1, 2 nu u_2, 2 nu u_3 (0 in 2D)
@@ -212,6 +215,7 @@ struct Scratch {
   uint8_t *xcc = nullptr;
   int32_t *qctr = nullptr;    // queue sweep: counters [kQueueCounterInts]
   int32_t *qflags = nullptr;  // queue sweep: done flags
+  int prog_pad = kProgPad;    // ints per progress counter of the 4x4 row pipeline
 };
 
 // Kernel launchers (dvm_sweep_diag.hip, dvm_sweep_rows.hip, dvm_iter.hip).
@@ -223,6 +227,18 @@ hipError_t launch_sweep(const Batch<T> &B, int diag, hipStream_t st);
 // chain's bands run on one XCD (checked with launch_xcd_probe).
 template <typename T>
 hipError_t launch_sweep_rows(const Batch<T> &B, bool local, hipStream_t st, const Scratch &scr = Scratch{});
+// The same with 4 x 4 tiles, stencil rule 1 and diffuse walls (every collision
+// model), as launch_sweep_rows forwards it; blocks of rows4_threads threads.
+template <typename T>
+bool uses_rows4(const Batch<T> &B) {
+  return B.tile_edge == 4 && !B.y2wall && !B.maxwell;
+}
+constexpr int rows4_threads() { return kWave * (band_waves(4) + 1); }
+template <typename T>
+hipError_t launch_sweep_rows4(const Batch<T> &B, bool local, hipStream_t st, const Scratch &scr);
+// launch_progress_reset for its counters in a scratch region (scr.prog_pad ints each).
+template <typename T>
+hipError_t launch_rows4_reset(const Batch<T> &B, const Scratch &scr, hipStream_t st);
 // The strip pipeline (2D, one launch for all problems of the batch).
 template <typename T>
 hipError_t launch_sweep_strips(const Batch<T> &B, hipStream_t st, const Scratch &scr = Scratch{});

@@ -525,8 +525,7 @@ void launch_rows_local(const Batch<T> &B, dim3 grid, hipStream_t st, const Scrat
   else PDVM_ROWS(TTV, false, 4)
   if (B.tile_edge == 4) {
     if (B.maxwell) { PDVM_ROWS_MW(4); }
-    else if (B.y2wall) { PDVM_ROWS_EXT(4, true); }
-    else { PDVM_ROWS_EXT(4, false); }
+    else { PDVM_ROWS_EXT(4, true); }  // stencil rule 1: sweep_rows4_kernel
   } else {
     if (B.maxwell) { PDVM_ROWS_MW(8); }
     else if (B.y2wall) { PDVM_ROWS_EXT(8, true); }
@@ -539,6 +538,7 @@ void launch_rows_local(const Batch<T> &B, dim3 grid, hipStream_t st, const Scrat
 
 template <typename T>
 hipError_t launch_sweep_rows(const Batch<T> &B, bool local, hipStream_t st, const Scratch &scr) {
+  if (uses_rows4(B)) return launch_sweep_rows4<T>(B, local, st, scr);
   const dim3 grid((unsigned)B.h_row_off[B.nprob]);
   if (local) launch_rows_local<T, true>(B, grid, st, scr);
   else launch_rows_local<T, false>(B, grid, st, scr);
