@@ -55,8 +55,6 @@ int64_t logical_params() {
   return n;
 }
 
-constexpr int kPixPerSplit = 4096;
-
 }  // namespace
 
 struct pdvm_unet {
@@ -75,9 +73,9 @@ struct pdvm_unet {
   uint16_t *act[NACT] = {};
   float *gact[NACT] = {};
   uint8_t *pidx[3] = {};
-  float *pred = nullptr, *dcat = nullptr, *part = nullptr, *bpart = nullptr, *loss_part = nullptr;
-  uint16_t *gbuf = nullptr;
-  int64_t part_n = 0, bpart_n = 0;
+  float *pred = nullptr, *dcat[3] = {}, *part = nullptr, *loss_part = nullptr;  // dcat: per decoder level (0 = finest)
+  uint16_t *gbuf[2] = {};  // bf16 gradients at a layer's output, of this layer and the next below
+  int64_t part_n = 0;
   int loss_blocks = 0;
   // training set (slot smax is the inference slot)
   uint8_t *ds_solid = nullptr;
@@ -192,21 +190,22 @@ int forward(pdvm_unet *n, const Slots &sl, int B) {
   return PDVM_OK;
 }
 
-// Backward pass from the bf16 gradient at the head output (n->gbuf).
+// Backward pass from the bf16 gradient at the head output (n->gbuf[0]). Each
+// layer's gradient arrives in one of the two buffers, already gated by the ReLU,
+// and the layer below's is left in the other: by the convolution's epilogue, or
+// by the kernels that undo a concatenation or a pooling.
 int backward(pdvm_unet *n, int B) {
   hipStream_t st = n->stream;
+  int cur = 0;
   for (int l = kLayers - 1; l >= 0; --l) {
     const LayerDef &L = kLayer[l];
     const int lev = level_of(l);
     const int rows = rows_of(l);
     const int cin = cin_of(l);
-    const int64_t P = n->pix(B, lev);
-    // gradient at this layer's pre-activation: for l < head, from its output's gradient
-    if (L.out >= 0) UCHK(n, launch_relu_grad(n->gact[L.out], n->act[L.out], P * L.cout, n->gbuf, st));
-    // weight gradient
+    uint16_t *const g = n->gbuf[cur], *const below = n->gbuf[cur ^ 1];
+    // weight and bias gradients
     WgradArgs w{};
-    w.g = n->gbuf;
-    w.gstride = rows;
+    w.g = g;
     w.M = rows;
     w.xa = n->act[L.in_a];
     w.xb = L.in_b >= 0 ? n->act[L.in_b] : nullptr;
@@ -217,24 +216,26 @@ int backward(pdvm_unet *n, int B) {
     w.B = B;
     w.H = n->H(lev);
     w.W = n->W(lev);
-    w.pix_per_split = kPixPerSplit;
-    const int splits = (int)((P + kPixPerSplit - 1) / kPixPerSplit);
-    const int64_t nw = (int64_t)rows * L.taps * cin;
-    if ((int64_t)splits * nw > n->part_n) return n->fail(PDVM_E_INVAL, "internal: partial buffer too small");
+    const WgradPlan plan = wgrad_plan(rows, w.Ca, w.Cb, L.taps, B, w.H, w.W);
+    w.pw = plan.pw;
+    w.npx = plan.npx;
+    w.npy = plan.npy;
+    w.patches = plan.patches;
+    w.per_split = plan.per_split;
+    const int64_t nw = (int64_t)rows * (L.taps * cin + 1);  // the biases follow the weights
+    if (plan.splits * nw > n->part_n) return n->fail(PDVM_E_INVAL, "internal: partial buffer too small");
     w.part = n->part;
     UCHK(n, mfma_begin(n));
-    UCHK(n, launch_wgrad(w, splits, st));
+    UCHK(n, launch_wgrad(w, plan, st));
     UCHK(n, mfma_end(n));
-    UCHK(n, launch_sum_splits(n->part, splits, nw, n->grads + n->offw[l], st));
-    const int csplits = (int)((P + kColsumPix - 1) / kColsumPix);
-    if ((int64_t)csplits * rows > n->bpart_n) return n->fail(PDVM_E_INVAL, "internal: bias partial buffer too small");
-    UCHK(n, launch_colsum(n->gbuf, P, rows, rows, n->bpart, csplits, st));
-    UCHK(n, launch_sum_splits(n->bpart, csplits, rows, n->grads + n->offb[l], st));
+    UCHK(n, launch_sum_splits(n->part, plan.splits, nw, n->grads + n->offw[l], st));
     if (l == 0) break;
     // input gradient: a convolution of the output gradient with the flipped, transposed weights
     UCHK(n, launch_wt_back(n->wbf + n->offw[l], rows, cin, L.taps, n->wback, st));
+    const int pin = L.in_a;
+    const bool cat = L.in_b >= 0, pooled = pin == P1 || pin == P2 || pin == P3;
     ConvArgs a{};
-    a.xa = n->gbuf;
+    a.xa = g;
     a.Ca = rows;
     a.wt = n->wback;
     a.nrows = cin;
@@ -244,24 +245,26 @@ int backward(pdvm_unet *n, int B) {
     a.W = n->W(lev);
     a.nstore = cin;
     a.ystride = cin;
-    const bool cat = L.in_b >= 0;
-    a.yf = cat ? n->dcat : n->gact[L.in_a];
+    if (cat) {
+      a.yf = n->dcat[lev];
+    } else if (pooled) {
+      a.yf = n->gact[pin];
+    } else {
+      a.yb = below;
+      a.gate = n->act[pin];
+    }
     UCHK(n, mfma_begin(n));
     UCHK(n, launch_conv(a, st));
     UCHK(n, mfma_end(n));
-    if (cat) {
-      UCHK(n, launch_concat_back(n->dcat, B, n->H(lev), n->W(lev), kAct[L.in_a].ch, kAct[L.in_b].ch,
-                                 n->gact[L.in_a], n->gact[L.in_b], st));
-    }
-    // a pooled input routes its gradient to the pooled tensor (added to the skip gradient)
-    const int pin = L.in_a;
-    if (!cat && (pin == P1 || pin == P2 || pin == P3)) {
-      const int k = pin == P1 ? 0 : (pin == P2 ? 1 : 2);
+    if (cat) UCHK(n, launch_up_grad(n->dcat[lev], n->act[pin], B, a.H, a.W, kAct[pin].ch, cin, below, st));
+    if (pooled) {
+      const int k = pin == P1 ? 0 : (pin == P2 ? 1 : 2);  // the level of the pooled tensor's source
       const Act src = pin == P1 ? E1 : (pin == P2 ? E2 : E3);
-      const int slev = kAct[src].level;
-      UCHK(n, launch_maxpool_back(n->gact[pin], n->pidx[k], B, n->H(slev), n->W(slev), kAct[src].ch, n->gact[src],
-                                  st));
+      const int cs = kAct[src].ch, ca = kAct[kLayer[12 - 2 * k].in_a].ch;  // dec1a, dec2a, dec3a take E1, E2, E3
+      UCHK(n, launch_pool_skip_grad(n->dcat[k], ca, ca + cs, n->gact[pin], n->pidx[k], n->act[src], B, n->H(k), n->W(k),
+                                    cs, below, st));
     }
+    cur ^= 1;
   }
   return PDVM_OK;
 }
@@ -274,7 +277,7 @@ int refresh_bf16(pdvm_unet *n) {
 int loss_and_backward(pdvm_unet *n, const Slots &sl, int B, double *loss) {
   const int64_t HW = (int64_t)n->n1 * n->n2;
   const int nblk = (int)((B * HW + 255) / 256);
-  UCHK(n, launch_loss(n->pred, n->ds_solid, n->ds_target, n->ds_wsamp, sl, B, n->n2, n->n1, n->gbuf, n->loss_part,
+  UCHK(n, launch_loss(n->pred, n->ds_solid, n->ds_target, n->ds_wsamp, sl, B, n->n2, n->n1, n->gbuf[0], n->loss_part,
                       nblk, n->stream));
   int rc = backward(n, B);
   if (rc != PDVM_OK) return rc;
@@ -366,18 +369,14 @@ int pdvm_unet_create(int32_t n1, int32_t n2, int32_t batch_max, int32_t dataset_
   n->np = o;
   int64_t wback_max = 0;
   for (int l = 1; l < kLayers; ++l) wback_max = std::max(wback_max, (int64_t)rows_of(l) * kLayer[l].taps * cin_of(l));
-  // partial buffers for the weight gradients
+  // partial buffer for the weight gradients
   for (int l = 0; l < kLayers; ++l) {
-    const int64_t P = n->pix(batch_max, level_of(l));
-    const int64_t splits = (P + kPixPerSplit - 1) / kPixPerSplit;
-    n->part_n = std::max(n->part_n, splits * rows_of(l) * kLayer[l].taps * cin_of(l));
-    n->bpart_n = std::max(n->bpart_n, (P + kColsumPix - 1) / kColsumPix * rows_of(l));
+    const int cb = kLayer[l].in_b >= 0 ? kAct[kLayer[l].in_b].ch : 0;
+    const WgradPlan p = wgrad_plan(rows_of(l), cin_of(l) - cb, cb, kLayer[l].taps, batch_max, n->H(level_of(l)), n->W(level_of(l)));
+    n->part_n = std::max(n->part_n, (int64_t)p.max_splits * rows_of(l) * (kLayer[l].taps * cin_of(l) + 1));
   }
   const int64_t HW = (int64_t)n1 * n2;
   n->loss_blocks = (int)((batch_max * HW + 255) / 256);
-  int64_t dcat_n = 0;
-  for (int l = 0; l < kLayers; ++l)
-    if (kLayer[l].in_b >= 0) dcat_n = std::max(dcat_n, n->pix(batch_max, level_of(l)) * cin_of(l));
   // arena layout
   std::vector<std::pair<void **, size_t>> plan;
   auto add = [&](void **p, size_t bytes) { plan.push_back({p, (bytes + 255) / 256 * 256}); };
@@ -390,15 +389,15 @@ int pdvm_unet_create(int32_t n1, int32_t n2, int32_t batch_max, int32_t dataset_
   for (int a = 0; a < NACT; ++a) {
     const size_t cnt = (size_t)n->pix(batch_max, kAct[a].level) * kAct[a].ch;
     add((void **)&n->act[a], 2 * cnt);
-    if (a != X) add((void **)&n->gact[a], 4 * cnt);
+    if (a == P1 || a == P2 || a == P3) add((void **)&n->gact[a], 4 * cnt);
   }
   for (int k = 0; k < 3; ++k) add((void **)&n->pidx[k], (size_t)n->pix(batch_max, k + 1) * kAct[P1 + 3 * k].ch);
   add((void **)&n->pred, sizeof(float) * batch_max * HW * 4);
-  add((void **)&n->dcat, sizeof(float) * dcat_n);
+  for (int k = 0; k < 3; ++k)
+    add((void **)&n->dcat[k], sizeof(float) * n->pix(batch_max, k) * cin_of(12 - 2 * k));
   add((void **)&n->part, sizeof(float) * n->part_n);
-  add((void **)&n->bpart, sizeof(float) * n->bpart_n);
   add((void **)&n->loss_part, sizeof(float) * n->loss_blocks);
-  add((void **)&n->gbuf, 2 * (size_t)batch_max * HW * 32);
+  for (int k = 0; k < 2; ++k) add((void **)&n->gbuf[k], 2 * (size_t)batch_max * HW * 32);
   add((void **)&n->ds_solid, (size_t)(dataset_max + 1) * HW);
   add((void **)&n->ds_feat, sizeof(float) * (dataset_max + 1));
   add((void **)&n->ds_target, sizeof(float) * (size_t)(dataset_max + 1) * 3 * HW);

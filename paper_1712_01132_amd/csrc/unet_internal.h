@@ -14,7 +14,7 @@ namespace pdvm_nn {
 
 constexpr int kMaxBatch = 32;
 constexpr int kInC = 8;  // input channels: solid, scaled log Kn, six zero pads
-constexpr int kColsumPix = 1024;  // rows per block of the column sums (bias gradients)
+constexpr int kWgradBlocks = 512;  // blocks of a weight-gradient launch: two per CU
 
 struct Slots {
   int32_t s[kMaxBatch];
@@ -36,35 +36,41 @@ struct ConvArgs {
   uint16_t *yb;        // bf16 output or null
   float *yf;           // fp32 output or null
   int nstore, ystride; // channels stored, channel stride of the output
+  const uint16_t *gate;  // null, or laid out as the output: where it is not positive, 0 is stored
 };
 
-// Weight gradient partials: part[split][m][k] = sum over the split's pixels of
-// G[p][m] * A[p][k], with G the bf16 gradient at the conv output (channel
-// stride gstride) and A the im2col matrix of the conv input.
+// Weight and bias gradient partials: part[split] = [M][taps * (Ca + Cb)] sums
+// over the split's pixels of G[p][m] * A[p][k], with G the bf16 gradient at the
+// conv output ([p][M]) and A the im2col matrix of the conv input, followed by the
+// M sums of G.
 struct WgradArgs {
   const uint16_t *g;
-  int gstride, M;      // M = output channels (rows of dW)
+  int M;               // output channels (a multiple of 32)
   const uint16_t *xa;
   const uint16_t *xb;
   int Ca, Cb, ups, taps;
   int B, H, W;
-  int pix_per_split;
-  float *part;         // [splits][M][K]
+  int pw, npx, npy, patches, per_split;  // from the plan
+  float *part;
 };
+// How a weight gradient is split: patches of 2^pw x (32 >> pw) pixels, npx x npy
+// per image; wm wavefronts of a block along the output channels, 16 cb input
+// channels per block, `splits` (at most max_splits, whatever the batch) partials.
+struct WgradPlan {
+  int wm, cb, pw, npx, npy, patches, per_split, splits, max_splits;
+};
+WgradPlan wgrad_plan(int M, int Ca, int Cb, int taps, int B, int H, int W);
 
 hipError_t launch_conv(const ConvArgs &a, hipStream_t st);
-hipError_t launch_wgrad(const WgradArgs &a, int splits, hipStream_t st);
+hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &p, hipStream_t st);
 hipError_t launch_sum_splits(const float *part, int splits, int64_t n, float *out, hipStream_t st);
-// splits = ceil(P / kColsumPix) blocks; part[split][C]
-hipError_t launch_colsum(const uint16_t *g, int64_t P, int C, int gstride, float *part, int splits, hipStream_t st);
 hipError_t launch_build_input(const uint8_t *solid_set, const float *feat_set, Slots sl, int B, int H, int W,
                               uint16_t *x, hipStream_t st);
-hipError_t launch_relu_grad(const float *dy, const uint16_t *y, int64_t n, uint16_t *g, hipStream_t st);
 hipError_t launch_maxpool(const uint16_t *x, int B, int H, int W, int C, uint16_t *y, uint8_t *idx, hipStream_t st);
-hipError_t launch_maxpool_back(const float *dy, const uint8_t *idx, int B, int H, int W, int C, float *dx,
-                               hipStream_t st);
-hipError_t launch_concat_back(const float *dcat, int B, int H, int W, int Ca, int Cb, float *da_half, float *db,
-                              hipStream_t st);
+hipError_t launch_up_grad(const float *dcat, const uint16_t *y, int B, int H, int W, int Ca, int C, uint16_t *g,
+                          hipStream_t st);
+hipError_t launch_pool_skip_grad(const float *dcat, int Ca, int C, const float *dp, const uint8_t *idx, const uint16_t *y,
+                                 int B, int H, int W, int Cs, uint16_t *g, hipStream_t st);
 hipError_t launch_loss(const float *pred, const uint8_t *solid_set, const float *target_set, const float *wsamp,
                        Slots sl, int B, int H, int W, uint16_t *g, float *part, int nblk, hipStream_t st);
 hipError_t launch_adam(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
