@@ -73,9 +73,9 @@ struct pdvm_unet {
   uint16_t *act[NACT] = {};
   float *gact[NACT] = {};
   uint8_t *pidx[3] = {};
-  float *pred = nullptr, *dcat[3] = {}, *part = nullptr, *loss_part = nullptr;  // dcat: per decoder level (0 = finest)
+  float *pred = nullptr, *dcat[3] = {}, *part = nullptr, *bpart = nullptr, *loss_part = nullptr;  // dcat: per decoder level (0 = finest)
   uint16_t *gbuf[2] = {};  // bf16 gradients at a layer's output, of this layer and the next below
-  int64_t part_n = 0;
+  int64_t part_n = 0, bpart_n = 0;
   int loss_blocks = 0;
   // training set (slot smax is the inference slot)
   uint8_t *ds_solid = nullptr;
@@ -216,19 +216,16 @@ int backward(pdvm_unet *n, int B) {
     w.B = B;
     w.H = n->H(lev);
     w.W = n->W(lev);
-    const WgradPlan plan = wgrad_plan(rows, w.Ca, w.Cb, L.taps, B, w.H, w.W);
-    w.pw = plan.pw;
-    w.npx = plan.npx;
-    w.npy = plan.npy;
-    w.patches = plan.patches;
-    w.per_split = plan.per_split;
-    const int64_t nw = (int64_t)rows * (L.taps * cin + 1);  // the biases follow the weights
-    if (plan.splits * nw > n->part_n) return n->fail(PDVM_E_INVAL, "internal: partial buffer too small");
+    const int64_t P = n->pix(B, lev), nw = (int64_t)rows * L.taps * cin;
+    const int splits = (int)((P + kPixPerSplit - 1) / kPixPerSplit), bsplits = (int)((P + kColsumPix - 1) / kColsumPix);
+    if (splits * nw > n->part_n || (int64_t)bsplits * rows > n->bpart_n)
+      return n->fail(PDVM_E_INVAL, "internal: partial buffer too small");
     w.part = n->part;
     UCHK(n, mfma_begin(n));
-    UCHK(n, launch_wgrad(w, plan, st));
+    UCHK(n, launch_wgrad(w, st));
     UCHK(n, mfma_end(n));
-    UCHK(n, launch_sum_splits(n->part, plan.splits, nw, n->grads + n->offw[l], st));
+    UCHK(n, launch_colsum(g, P, rows, n->bpart, st));
+    UCHK(n, launch_sum_splits(n->part, splits, nw, n->grads + n->offw[l], n->bpart, bsplits, rows, n->grads + n->offb[l], st));
     if (l == 0) break;
     // input gradient: a convolution of the output gradient with the flipped, transposed weights
     UCHK(n, launch_wt_back(n->wbf + n->offw[l], rows, cin, L.taps, n->wback, st));
@@ -369,11 +366,11 @@ int pdvm_unet_create(int32_t n1, int32_t n2, int32_t batch_max, int32_t dataset_
   n->np = o;
   int64_t wback_max = 0;
   for (int l = 1; l < kLayers; ++l) wback_max = std::max(wback_max, (int64_t)rows_of(l) * kLayer[l].taps * cin_of(l));
-  // partial buffer for the weight gradients
+  // partial buffers for the weight and bias gradients
   for (int l = 0; l < kLayers; ++l) {
-    const int cb = kLayer[l].in_b >= 0 ? kAct[kLayer[l].in_b].ch : 0;
-    const WgradPlan p = wgrad_plan(rows_of(l), cin_of(l) - cb, cb, kLayer[l].taps, batch_max, n->H(level_of(l)), n->W(level_of(l)));
-    n->part_n = std::max(n->part_n, (int64_t)p.max_splits * rows_of(l) * (kLayer[l].taps * cin_of(l) + 1));
+    const int64_t P = n->pix(batch_max, level_of(l));
+    n->part_n = std::max(n->part_n, (P + kPixPerSplit - 1) / kPixPerSplit * rows_of(l) * kLayer[l].taps * cin_of(l));
+    n->bpart_n = std::max(n->bpart_n, (P + kColsumPix - 1) / kColsumPix * rows_of(l));
   }
   const int64_t HW = (int64_t)n1 * n2;
   n->loss_blocks = (int)((batch_max * HW + 255) / 256);
@@ -396,6 +393,7 @@ int pdvm_unet_create(int32_t n1, int32_t n2, int32_t batch_max, int32_t dataset_
   for (int k = 0; k < 3; ++k)
     add((void **)&n->dcat[k], sizeof(float) * n->pix(batch_max, k) * cin_of(12 - 2 * k));
   add((void **)&n->part, sizeof(float) * n->part_n);
+  add((void **)&n->bpart, sizeof(float) * n->bpart_n);
   add((void **)&n->loss_part, sizeof(float) * n->loss_blocks);
   for (int k = 0; k < 2; ++k) add((void **)&n->gbuf[k], 2 * (size_t)batch_max * HW * 32);
   add((void **)&n->ds_solid, (size_t)(dataset_max + 1) * HW);

@@ -14,7 +14,8 @@ namespace pdvm_nn {
 
 constexpr int kMaxBatch = 32;
 constexpr int kInC = 8;  // input channels: solid, scaled log Kn, six zero pads
-constexpr int kWgradBlocks = 512;  // blocks of a weight-gradient launch: two per CU
+constexpr int kColsumPix = 1024;    // rows per partial of the bias gradients
+constexpr int kPixPerSplit = 4096;  // pixels per partial of the weight gradients
 
 struct Slots {
   int32_t s[kMaxBatch];
@@ -37,12 +38,15 @@ struct ConvArgs {
   float *yf;           // fp32 output or null
   int nstore, ystride; // channels stored, channel stride of the output
   const uint16_t *gate;  // null, or laid out as the output: where it is not positive, 0 is stored
+  // set by launch_conv: tiles of 2^pw columns, npx x npy per image; reciprocals of
+  // the chunks per pixel and of the patch's columns
+  int pw, npx, npy;
+  uint32_t div_ch, div_rw;
 };
 
-// Weight and bias gradient partials: part[split] = [M][taps * (Ca + Cb)] sums
-// over the split's pixels of G[p][m] * A[p][k], with G the bf16 gradient at the
-// conv output ([p][M]) and A the im2col matrix of the conv input, followed by the
-// M sums of G.
+// Weight gradient partials: part[split][m][k] = sum over the split's pixels of
+// G[p][m] * A[p][k], with G the bf16 gradient at the conv output ([p][M]) and A the
+// im2col matrix of the conv input.
 struct WgradArgs {
   const uint16_t *g;
   int M;               // output channels (a multiple of 32)
@@ -50,20 +54,18 @@ struct WgradArgs {
   const uint16_t *xb;
   int Ca, Cb, ups, taps;
   int B, H, W;
-  int pw, npx, npy, patches, per_split;  // from the plan
   float *part;
+  int xrows;               // set by launch_wgrad: padded pixels staged per run,
+  uint32_t div_w, div_wr;  // reciprocals of the image's width and padded width
 };
-// How a weight gradient is split: patches of 2^pw x (32 >> pw) pixels, npx x npy
-// per image; wm wavefronts of a block along the output channels, 16 cb input
-// channels per block, `splits` (at most max_splits, whatever the batch) partials.
-struct WgradPlan {
-  int wm, cb, pw, npx, npy, patches, per_split, splits, max_splits;
-};
-WgradPlan wgrad_plan(int M, int Ca, int Cb, int taps, int B, int H, int W);
 
 hipError_t launch_conv(const ConvArgs &a, hipStream_t st);
-hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &p, hipStream_t st);
-hipError_t launch_sum_splits(const float *part, int splits, int64_t n, float *out, hipStream_t st);
+hipError_t launch_wgrad(WgradArgs a, hipStream_t st);
+// ceil(P / kColsumPix) partials: part[.][C]
+hipError_t launch_colsum(const uint16_t *g, int64_t P, int C, float *part, hipStream_t st);
+// weight gradients from `splits` partials of n values, bias gradients from bsplits of nb
+hipError_t launch_sum_splits(const float *part, int splits, int64_t n, float *out, const float *bpart, int bsplits, int nb,
+                             float *outb, hipStream_t st);
 hipError_t launch_build_input(const uint8_t *solid_set, const float *feat_set, Slots sl, int B, int H, int W,
                               uint16_t *x, hipStream_t st);
 hipError_t launch_maxpool(const uint16_t *x, int B, int H, int W, int C, uint16_t *y, uint8_t *idx, hipStream_t st);

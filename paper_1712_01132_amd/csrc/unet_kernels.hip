@@ -26,358 +26,439 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-constexpr int kPitch = 40;  // LDS row pitch in bf16: 32 k values + 8 pad (conflict-free 16-byte reads)
-
-// One 8-channel group of the im2col matrix: row = output pixel (b, y, x),
-// columns k .. k+7 (k a multiple of 8). Zero outside the image along y (zero
-// padding), circular along x (the periodic flow axis), zero beyond K.
-struct Im2col {
-  const uint16_t *xa, *xb;
-  int Ca, Cb, ups, taps, H, W, K, Cin;
-  __device__ __forceinline__ uint4 load(int b, int y, int x, int k) const {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (k >= K) return v;
-    const int tap = k / Cin;
-    const int c = k - tap * Cin;
-    const int dy = taps == 9 ? tap / 3 - 1 : 0;
-    const int dx = taps == 9 ? tap % 3 - 1 : 0;
-    const int yy = y + dy;
-    if (yy < 0 || yy >= H) return v;
-    int xx = x + dx;
-    xx = xx < 0 ? xx + W : (xx >= W ? xx - W : xx);
-    const uint16_t *src;
-    if (c < Ca) {
-      src = ups ? xa + ((int64_t)((b * (H >> 1) + (yy >> 1)) * (W >> 1) + (xx >> 1))) * Ca + c
-                : xa + ((int64_t)((b * H + yy) * W + xx)) * Ca + c;
-    } else {
-      src = xb + ((int64_t)((b * H + yy) * W + xx)) * Cb + (c - Ca);
-    }
-    return *reinterpret_cast<const uint4 *>(src);
-  }
-};
-
-// out tile: 128 pixels x BN output channels, 4 wavefronts of 32 pixels each.
-template <int BN>
-__global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
-  __shared__ uint4 As[128 * kPitch / 8];
-  __shared__ uint4 Bs[BN * kPitch / 8];
+// Implicit-GEMM convolution. A block computes a tile of 64 WX pixels (2^pw
+// columns) x 32 WN output channels; each of its WX x WN wavefronts 64 pixels x 32
+// channels. The input patch with its one-pixel rim is staged in LDS once, with all its
+// channels (up to 384 of them in the 160 KB), so an input value is loaded once and not
+// once per tap, and the K loop (taps, then channels: the order of the sums) has no
+// barrier. Weights come straight from memory (the L1 serves the block's
+// wavefronts), four K steps ahead. The channels are the rows of the products and
+// the pixels their columns, so a lane ends with four consecutive channels of a
+// pixel: 8- or 16-byte stores. C8: 8 input channels, four taps per K step.
+// Bound per K step and CU: 16 KB of LDS reads, 8 KB of L1 reads and the matrix
+// products take 128 clocks each; and the staging, which nothing overlaps within a
+// block. Measured (MI355X): the 14 forward and 14 backward 3x3 convolutions of a
+// training step on 8 x 256^2 1.57 -> 1.0 ms, on 2 x 64^2 0.92 -> 0.45 ms, against
+// 128-pixel tiles that staged 32 im2col columns at a time behind two barriers.
+template <int WX, int WN, int TAPS, bool C8>
+__global__ void __launch_bounds__(64 * WX * WN) conv_kernel(ConvArgs a) {
+  constexpr int NT = 64 * WX * WN, RIM = TAPS == 9 ? 1 : 0;
+  extern __shared__ __attribute__((aligned(16))) unsigned char patch[];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int P = a.B * a.H * a.W;
-  const int p0 = blockIdx.x * 128;
-  const int n0 = blockIdx.y * BN;
-  const int Cin = a.Ca + a.Cb;
-  const int K = a.taps * Cin;
-  const int nk = (K + 31) / 32;
-  const Im2col im{a.xa, a.xb, a.Ca, a.Cb, a.ups, a.taps, a.H, a.W, K, Cin};
+  const int wx = wv % WX, wn = wv / WX;
+  const int PW = 1 << a.pw, PH = (64 * WX) >> a.pw, RW = PW + 2 * RIM, RR = (PH + 2 * RIM) * RW;
+  const int Cin = a.Ca + a.Cb, K = TAPS * Cin;
+  const int nch = Cin / 8;                          // 16-byte chunks of a pixel
+  const uint32_t pitch = (uint32_t)(Cin * 2 + 16);  // padded: the fragment reads of 16 pixels spread over the banks
+  const int tx = blockIdx.x % a.npx, tq = blockIdx.x / a.npx;
+  const int x0 = tx * PW, y0 = tq % a.npy * PH, b = tq / a.npy;
+  const int n0 = (blockIdx.y * WN + wn) * 32;
 
-  int pb[2], py[2], px[2];
-  bool pv[2];
+  // --- weights: rows n0 + 16 f + lane % 16, k = 32 ks + 8 (lane / 16) ..
+  constexpr int D = 4;
+  const uint16_t *wrow[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int p = p0 + (tid >> 2) + 64 * i;
-    pv[i] = p < P;
-    const int q = pv[i] ? p : 0;
-    px[i] = q % a.W;
-    const int t = q / a.W;
-    py[i] = t % a.H;
-    pb[i] = t / a.H;
-  }
-  const int kg = (tid & 3) * 8;
-  const int brow = tid >> 2;
-  const bool bload = brow < BN && n0 + brow < a.nrows;
-
-  uint4 ra[2], rb = make_uint4(0, 0, 0, 0);
-  auto gload = [&](int kt) {
-    const int k = kt * 32 + kg;
+  for (int f = 0; f < 2; ++f) wrow[f] = a.wt + (int64_t)min(n0 + 16 * f + (lane & 15), a.nrows - 1) * K + 8 * (lane >> 4);
+  const int nk = C8 ? (K + 31) / 32 : K / 32;
+  uint4 wr[D][2];
+  auto wload = [&](int ks, uint4(&r)[2]) __attribute__((always_inline)) {
+    const int k = min(ks, nk - 1);  // past the end: loaded again, not used
 #pragma unroll
-    for (int i = 0; i < 2; ++i) ra[i] = pv[i] ? im.load(pb[i], py[i], px[i], k) : make_uint4(0, 0, 0, 0);
-    rb = make_uint4(0, 0, 0, 0);
-    if (bload && k < K) rb = *reinterpret_cast<const uint4 *>(a.wt + (int64_t)(n0 + brow) * K + k);
+    for (int f = 0; f < 2; ++f) {
+      r[f] = make_uint4(0, 0, 0, 0);
+      if (!C8 || 32 * k + 8 * (lane >> 4) < K) r[f] = *reinterpret_cast<const uint4 *>(wrow[f] + 32 * k);
+    }
   };
+#pragma unroll
+  for (int d = 0; d < D; ++d) wload(d, wr[d]);
 
-  f32x4 acc[2][BN / 16];
+  // --- the input patch: zero outside the image along y, circular along x
+  {
+    const int total = RR * nch;
+    constexpr int U = 8;  // loads in flight per lane
+    for (int e0 = tid; e0 < total; e0 += NT * U) {
+      uint4 v[U];
+      uint32_t to[U];
 #pragma unroll
-  for (int ms = 0; ms < 2; ++ms)
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * NT;
+        const int r = C8 ? e : (int)__umulhi((uint32_t)e, a.div_ch), ch = e - r * nch;  // e / nch (e < 2^16)
+        const int ry = (int)__umulhi((uint32_t)r, a.div_rw), rx = r - ry * RW;   // r / RW
+        const int y = y0 + ry - RIM;
+        int x = x0 + rx - RIM;
+        const bool in = e < total && y >= 0 && y < a.H && x <= a.W;  // right of a ragged last tile: nothing to read
+        x = x < 0 ? x + a.W : (x >= a.W ? x - a.W : x);
+        to[u] = e < total ? (uint32_t)r * pitch + 16u * ch : ~0u;
+        v[u] = make_uint4(0, 0, 0, 0);
+        if (in) {
+          const int c = 8 * ch;
+          const uint16_t *src;
+          if (c < a.Ca)
+            src = a.ups ? a.xa + ((int64_t)(b * (a.H >> 1) + (y >> 1)) * (a.W >> 1) + (x >> 1)) * a.Ca + c
+                        : a.xa + ((int64_t)(b * a.H + y) * a.W + x) * a.Ca + c;
+          else
+            src = a.xb + ((int64_t)(b * a.H + y) * a.W + x) * a.Cb + (c - a.Ca);
+          v[u] = *reinterpret_cast<const uint4 *>(src);
+        }
+      }
 #pragma unroll
-    for (int ns = 0; ns < BN / 16; ++ns) acc[ms][ns] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int u = 0; u < U; ++u)
+        if (to[u] != ~0u) *reinterpret_cast<uint4 *>(patch + to[u]) = v[u];
+    }
+  }
+  __syncthreads();
 
-  gload(0);
-  for (int kt = 0; kt < nk; ++kt) {
-    __syncthreads();
+  // --- pixel fragments: pixel t = 64 wx + 16 f + lane % 16 of the tile
+  uint32_t pb[4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) As[((tid >> 2) + 64 * i) * (kPitch / 8) + (tid & 3)] = ra[i];
-    if (brow < BN) Bs[brow * (kPitch / 8) + (tid & 3)] = rb;
-    __syncthreads();
-    if (kt + 1 < nk) gload(kt + 1);
-    bf16x8 fa[2], fb[BN / 16];
+  for (int f = 0; f < 4; ++f) {
+    const int t = 64 * wx + 16 * f + (lane & 15);
+    pb[f] = (uint32_t)((t >> a.pw) * RW + (t & (PW - 1))) * pitch + (C8 ? 0u : 16u * (lane >> 4));
+  }
+  f32x4 acc[2][4];
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
-      fa[ms] = __builtin_bit_cast(bf16x8, As[(32 * wv + 16 * ms + (lane & 15)) * (kPitch / 8) + (lane >> 4)]);
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int ns = 0; ns < BN / 16; ++ns)
-      fb[ns] = __builtin_bit_cast(bf16x8, Bs[(16 * ns + (lane & 15)) * (kPitch / 8) + (lane >> 4)]);
+    for (int f = 0; f < 4; ++f) acc[m][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  uint4 pr[2][4];
+  // K step ks: tap ks / (Cin / 32) at channels 32 (ks % (Cin / 32)); its offset into the patch advances with ks
+  uint32_t ko = 0;
+  int kc = 0, kt = 0;
+  const int ncs = Cin / 32;
+  auto pload = [&](int ks, uint4(&r)[4]) __attribute__((always_inline)) {
+    if (C8) {
+      const int t = 4 * ks + (lane >> 4);
+      const uint32_t o = (uint32_t)(t / 3 * RW + t % 3) * pitch;
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
+      for (int f = 0; f < 4; ++f)
+        r[f] = t < TAPS ? *reinterpret_cast<const uint4 *>(patch + pb[f] + o) : make_uint4(0, 0, 0, 0);
+      return;
+    }
 #pragma unroll
-      for (int ns = 0; ns < BN / 16; ++ns)
-        acc[ms][ns] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ms], fb[ns], acc[ms][ns], 0, 0, 0);
+    for (int f = 0; f < 4; ++f) r[f] = *reinterpret_cast<const uint4 *>(patch + pb[f] + ko);
+    ko += 64;
+    if (++kc == ncs) {  // the next tap (past the last one: the patch's first pixel, not used)
+      kc = 0;
+      kt = kt + 1 == TAPS ? 0 : kt + 1;
+      ko = (uint32_t)(kt / 3 * RW + kt % 3) * pitch;
+    }
+  };
+  pload(0, pr[0]);
+  for (int k0 = 0; k0 < nk; k0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (k0 + d < nk) {
+        pload(k0 + d + 1, pr[(d + 1) & 1]);
+        bf16x8 fw[2], fp[4];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) fw[m] = __builtin_bit_cast(bf16x8, wr[d][m]);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) fp[f] = __builtin_bit_cast(bf16x8, pr[d & 1][f]);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int f = 0; f < 4; ++f)
+            acc[m][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[m], fp[f], acc[m][f], 0, 0, 0);
+        wload(k0 + d + D, wr[d]);
+      }
+    }
   }
 
+  // --- D[m = 4 (lane / 16) + r][n = lane % 16]: channels n0 + 16 m + 4 (lane / 16) + r of pixel 16 f + lane % 16
 #pragma unroll
-  for (int ns = 0; ns < BN / 16; ++ns) {
-    const int n = n0 + 16 * ns + (lane & 15);
-    if (n >= a.nstore) continue;
-    const float bias = a.bias ? a.bias[n] : 0.f;
+  for (int f = 0; f < 4; ++f) {
+    const int t = 64 * wx + 16 * f + (lane & 15);
+    const int y = y0 + (t >> a.pw), x = x0 + (t & (PW - 1));
+    if (y >= a.H || x >= a.W) continue;
+    const int64_t p = (int64_t)(b * a.H + y) * a.W + x;
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
+    for (int m = 0; m < 2; ++m) {
+      const int n = n0 + 16 * m + 4 * (lane >> 4);
+      if (n >= a.nstore) continue;
+      f32x4 v = acc[m][f];
+      if (a.bias) v += *reinterpret_cast<const f32x4 *>(a.bias + n);
+      if (a.relu) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int p = p0 + 32 * wv + 16 * ms + 4 * (lane >> 4) + r;
-        if (p >= P) continue;
-        float v = acc[ms][ns][r] + bias;
-        if (a.relu) v = fmaxf(v, 0.f);
-        if (a.gate) v = bf2f(a.gate[(int64_t)p * a.ystride + n]) > 0.f ? v : 0.f;
-        if (a.yb) a.yb[(int64_t)p * a.ystride + n] = f2bf(v);
-        else a.yf[(int64_t)p * a.ystride + n] = v;
+        for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
       }
+      const int64_t at = p * a.ystride + n;
+      if (a.gate) {
+        const uint2 gw = *reinterpret_cast<const uint2 *>(a.gate + at);
+        v[0] = bf2f((uint16_t)gw.x) > 0.f ? v[0] : 0.f;
+        v[1] = bf2f((uint16_t)(gw.x >> 16)) > 0.f ? v[1] : 0.f;
+        v[2] = bf2f((uint16_t)gw.y) > 0.f ? v[2] : 0.f;
+        v[3] = bf2f((uint16_t)(gw.y >> 16)) > 0.f ? v[3] : 0.f;
+      }
+      if (n + 4 > a.nstore) {  // the head: 3 of 4 channels
+        for (int r = 0; r < 4 && n + r < a.nstore; ++r) {
+          if (a.yb) a.yb[at + r] = f2bf(v[r]);
+          else a.yf[at + r] = v[r];
+        }
+      } else if (a.yb) {
+        *reinterpret_cast<uint2 *>(a.yb + at) = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                                                           (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+      } else {
+        *reinterpret_cast<f32x4 *>(a.yf + at) = v;
+      }
+    }
   }
 }
 
-// dW partials. A wavefront owns 32 output channels x (all taps x 16 CB input
-// channels), reduced over patches of 32 pixels (2^pw columns x 32 / 2^pw rows of
-// one image); a block is WM wavefronts along the output channels x 4 / WM along
-// the patches. Both operands are pixel-major in memory while the matrix
-// instruction wants 8 consecutive pixels of one channel per lane: they are
-// staged in LDS as they are (rows of pixels) and read with the transposing LDS
-// load (ds_read_b64_tr_b16: lane l of 16 gets column l of 4 rows of 16 values).
-// The input patch is staged once with its one-pixel rim, and each tap reads it
-// at a shifted pixel; so a block reads the output gradient once per 16 CB input
-// channels (not once per 32 im2col columns) and the input once (not per tap).
-// The bias gradient is one more product, with a matrix of ones, in the blocks
-// of the first input channels. With WM < 4 the wavefronts of one channel range add
-// their sums through LDS at the end.
-// Bound: the LDS reads (40 transposing loads per 36 matrix products of a patch).
-// Measured (MI355X, training step on 8 x 256^2): all weight and bias gradients
-// 0.67 ms, against 3.25 ms with 64 x 32 tiles transposed by 16-bit LDS writes and
-// 1.4 ms of column sums; adding up the splits 0.17 ms, against 0.97.
-constexpr int kPatch = 32;
+// dW partials of kPixPerSplit pixels each. A wavefront owns 32 output channels x
+// 16 input channels x the three taps of one row of the stencil; a block is WM
+// wavefronts along the output and WC along the input channels, for one stencil
+// row (blockIdx.z % 3). Both operands are pixel-major in memory while the matrix
+// instruction wants 8 consecutive pixels of one channel per lane: they are staged
+// in LDS as they are (rows of pixels) and read with the transposing LDS load
+// (ds_read_b64_tr_b16: lane l of 16 gets column l of 4 rows of 16 values).
+// kRun pixels are staged at a time, two buffers, the next run's loads in flight.
+// Of the input, a run is the contiguous stretch of the image's rows padded by a
+// pixel on either side (the wrapped neighbours), so the three taps read it at
+// offsets 0, 1 and 2: pixel k of the run, i rows into it, is padded pixel k + 2 i.
+// The sums' order (32 pixels per product, products in pixel order, splits in
+// order) does not depend on the tiles.
+// Bound: the instructions of one wavefront per run (addresses, staging, 20
+// transposing loads per 6 matrix products), as the order leaves only P /
+// kPixPerSplit runs of work side by side. Measured (MI355X, training step on 8 x
+// 256^2): all weight gradients 1.0 ms, against 3.25 ms with 64 x 32 tiles
+// transposed by 16-bit LDS writes; 0.67 ms with the patches of a split spread over
+// wavefronts in another order of sums, which a few steps of Adam (whose update is
+// nearly the sign of a small gradient) turn into differences of 1e-2.
+constexpr int kRun = 128;
 
 typedef short v4s __attribute__((ext_vector_type(4)));
-typedef short v8s __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ v4s tr_read(uint32_t addr) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)addr);
-}
 __device__ __forceinline__ bf16x8 tr_pair(uint32_t a0, uint32_t a1) {
-  const v4s lo = tr_read(a0), hi = tr_read(a1);
+  using lp = __attribute__((address_space(3))) v4s *;
+  const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(uintptr_t)a0);
+  const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(uintptr_t)a1);
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-template <int TAPS, int WM, int CB>
-__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
-  constexpr int WP = 4 / WM, BM = 32 * WM, BC = 16 * CB;
-  constexpr int RIM = TAPS == 9 ? 1 : 0;
-  constexpr int XROWS = TAPS == 9 ? 102 : 32;           // pixels of a patch with its rim, at most (32 x 1)
-  constexpr int XP = BC * 2 + 16, GP = BM * 2 + 16;     // LDS row pitches in bytes
-  constexpr int XCH = BC / 8, GCH = BM / 8;             // 16-byte chunks per pixel
-  constexpr int XN = (WP * XROWS * XCH + 255) / 256, GN = WP * kPatch * GCH / 256;
-  constexpr int XBYTES = WP * XROWS * XP, GBYTES = WP * kPatch * GP;
-  constexpr int REDUCE = WP > 1 ? WM * TAPS * CB * 256 * 4 : 0;  // bytes of one 16-row half of the sums
-  __shared__ __attribute__((aligned(16))) unsigned char lds[XBYTES + GBYTES > REDUCE ? XBYTES + GBYTES : REDUCE];
-  __shared__ int4 base[2][WP];
+// TX: taps per stencil row (3, or 1 for 1x1); XN: 16-byte pieces of a run's input per thread
+template <int TX, int WM, int WC, int XN>
+__global__ void __launch_bounds__(64 * WM * WC) wgrad_kernel(WgradArgs a) {
+  constexpr int NT = 64 * WM * WC, BM = 32 * WM, BC = 16 * WC;
+  constexpr int RIM = TX == 3 ? 1 : 0;
+  constexpr int XP = BC * 2 + 16, GP = BM * 2 + 16;  // LDS row pitches in bytes
+  constexpr int XCH = BC / 8, GCH = BM / 8;          // 16-byte pieces per pixel
+  constexpr int GN = kRun * GCH / NT;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const uint32_t l0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wm = wv % WM, wp = wv / WM;
-  const int PW = 1 << a.pw, PH = kPatch >> a.pw, RW = PW + 2 * RIM, RR = (PH + 2 * RIM) * RW;
+  const int wm = wv % WM, wc = wv / WM;
   const int m0 = blockIdx.x * BM, c0 = blockIdx.y * BC;
-  const int qbeg = blockIdx.z * a.per_split, qend = min(a.patches, qbeg + a.per_split);
-  const int Cin = a.Ca + a.Cb;
+  const int dy = TX == 3 ? (int)(blockIdx.z % 3) - 1 : 0, split = TX == 3 ? blockIdx.z / 3 : blockIdx.z;
+  const int Cin = a.Ca + a.Cb, H = a.H, W = a.W, WR = W + 2 * RIM;
+  const int P = a.B * H * W;
+  const int pbeg = split * kPixPerSplit, pend = min(P, pbeg + kPixPerSplit);
+  const uint32_t xbytes = (uint32_t)a.xrows * XP, bufbytes = xbytes + kRun * GP;
   // this block's channels come from one of the concatenated inputs
   const bool inA = c0 < a.Ca;
   const uint16_t *const xs = inA ? a.xa : a.xb;
   const int xc = inA ? c0 : c0 - a.Ca, xC = inA ? a.Ca : a.Cb;
   const int ups = inA ? a.ups : 0;
 
-  // the pixel within a patch and the 16-byte chunk of each staged piece
-  int xslot[XN], xry[XN], xrx[XN], xch[XN];
-  uint32_t xto[XN];
-#pragma unroll
-  for (int i = 0; i < XN; ++i) {
-    const int e = tid + 256 * i, px = e / XCH;
-    xch[i] = e % XCH;
-    const int sl = px / XROWS, r = px % XROWS;
-    const bool ok = sl < WP && r < RR && xc + xch[i] * 8 < xC;
-    xslot[i] = ok ? sl : -1;
-    xry[i] = r / RW - RIM;
-    xrx[i] = r % RW - RIM;
-    xto[i] = sl < WP ? (uint32_t)((sl * XROWS + r) * XP + xch[i] * 16) : ~0u;
-  }
-  int gslot[GN], gpy[GN], gpx[GN], gch[GN];
-#pragma unroll
-  for (int i = 0; i < GN; ++i) {
-    const int e = tid + 256 * i, px = e / GCH;
-    gch[i] = e % GCH;
-    gslot[i] = px / kPatch;
-    gpy[i] = (px % kPatch) >> a.pw;
-    gpx[i] = (px % kPatch) & (PW - 1);
-  }
-  // first pixel of patch q (its image, row and column; image -1 past the end)
-  auto locate = [&](int q, int buf) {
-    if (tid < WP) {
-      const int qq = q + tid;
-      const int x = qq % a.npx, t = qq / a.npx;
-      base[buf][tid] = qq < qend ? make_int4(t / a.npy, t % a.npy * PH, x * PW, 0) : make_int4(-1, 0, 0, 0);
-    }
+  // a quotient of small numbers (below 2^16), or of ones below 2 d
+  auto quot = [](int v, int d, uint32_t magic) {
+    return d == 1 ? v : (magic ? (int)__umulhi((uint32_t)v, magic) : (v >= d ? 1 : 0));
   };
-  uint4 rx[XN], rg[GN];
-  auto load = [&](int buf) {
+  constexpr int AHEAD = 2;  // runs whose loads are in flight
+  struct Run {
+    uint4 x[XN], g[GN];
+  } runs[AHEAD];
+  // the next run to load: its first pixel, and that pixel's column, row and image
+  int lp = pbeg, lx = pbeg % W, ly = pbeg / W % H, lb = pbeg / W / H;
+  const char *const xbase = reinterpret_cast<const char *>(xs + xc), *const gbase = reinterpret_cast<const char *>(a.g + m0);
+  // byte offsets fit in 32 bits (a tensor has under 2^31 values)
+  auto load = [&](Run &R) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < XN; ++i) {
-      rx[i] = make_uint4(0, 0, 0, 0);
-      const int4 b = base[buf][max(xslot[i], 0)];
-      const int y = b.y + xry[i];
-      int x = b.z + xrx[i];
-      // circular along x; past the right rim of a ragged last patch there is nothing to read
-      const bool in = xslot[i] >= 0 && b.x >= 0 && y >= 0 && y < a.H && x <= a.W;
-      x = x < 0 ? x + a.W : (x >= a.W ? x - a.W : x);
-      if (in) {
-        const int64_t p = ups ? (int64_t)(b.x * (a.H >> 1) + (y >> 1)) * (a.W >> 1) + (x >> 1)
-                              : (int64_t)(b.x * a.H + y) * a.W + x;
-        rx[i] = *reinterpret_cast<const uint4 *>(xs + p * xC + xc + xch[i] * 8);
+      const int e = tid + NT * i, l = e / XCH, ch = e % XCH;
+      R.x[i] = make_uint4(0, 0, 0, 0);
+      const int u = l + lx, row = quot(u, WR, a.div_wr);
+      int x = u - row * WR - RIM, y = ly + row, b = lb;
+      if (y >= H) {  // past this image
+        const int q = y >= 2 * H ? y / H : 1;
+        b += q;
+        y -= q * H;
+      }
+      y += dy;
+      x = x < 0 ? x + W : (x >= W ? x - W : x);
+      if (l < a.xrows && b < a.B && y >= 0 && y < H && xc + 8 * ch < xC) {
+        const uint32_t p = ups ? (uint32_t)((b * (H >> 1) + (y >> 1)) * (W >> 1) + (x >> 1)) : (uint32_t)((b * H + y) * W + x);
+        R.x[i] = *reinterpret_cast<const uint4 *>(xbase + (uint32_t)(p * (uint32_t)(2 * xC) + 16u * ch));
       }
     }
 #pragma unroll
     for (int i = 0; i < GN; ++i) {
-      rg[i] = make_uint4(0, 0, 0, 0);
-      const int4 b = base[buf][gslot[i]];
-      const int y = b.y + gpy[i], x = b.z + gpx[i];
-      if (b.x >= 0 && y < a.H && x < a.W)
-        rg[i] = *reinterpret_cast<const uint4 *>(a.g + ((int64_t)(b.x * a.H + y) * a.W + x) * a.M + m0 + gch[i] * 8);
+      const int e = tid + NT * i, k = e / GCH, ch = e % GCH;
+      R.g[i] = make_uint4(0, 0, 0, 0);
+      if (lp + k < pend) R.g[i] = *reinterpret_cast<const uint4 *>(gbase + (uint32_t)((uint32_t)(lp + k) * (uint32_t)(2 * a.M) + 16u * ch));
+    }
+    if (lp + kRun >= pend) return;  // the last run: loaded again, not used
+    const int t = lx + kRun, rows = quot(t, W, a.div_w);
+    lp += kRun;
+    lx = t - rows * W;
+    ly += rows;
+    while (ly >= H) {
+      ly -= H;
+      ++lb;
     }
   };
-  // fragment addresses: pixel k = 8 (lane / 16) + 4 h + (lane % 16) / 4, columns 4 (lane % 4) ..
+  auto store = [&](uint32_t buf, const Run &R) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < XN; ++i) {
+      const int e = tid + NT * i;
+      if (e < a.xrows * XCH) *reinterpret_cast<uint4 *>(lds + buf + e / XCH * XP + e % XCH * 16) = R.x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < GN; ++i) {
+      const int e = tid + NT * i;
+      *reinterpret_cast<uint4 *>(lds + buf + xbytes + e / GCH * GP + e % GCH * 16) = R.g[i];
+    }
+  };
+  f32x4 acc[2][TX];
+#pragma unroll
+  for (int ms = 0; ms < 2; ++ms)
+#pragma unroll
+    for (int t = 0; t < TX; ++t) acc[ms][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // fragments: pixel k = 32 c + 8 (lane / 16) + 4 h + (lane % 16) / 4, columns 4 (lane % 4) ..
   const int kr = 8 * (lane >> 4) + ((lane & 15) >> 2), cq = 4 * (lane & 3);
-  uint32_t ga[2], xa[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int k = kr + 4 * h;
-    ga[h] = l0 + XBYTES + (uint32_t)((wp * kPatch + k) * GP + (wm * 32 + cq) * 2);
-    xa[h] = l0 + (uint32_t)((wp * XROWS + (k >> a.pw) * RW + (k & (PW - 1))) * XP + cq * 2);
-  }
-  uint32_t toff[TAPS];
-#pragma unroll
-  for (int t = 0; t < TAPS; ++t) toff[t] = (uint32_t)((t / 3 * RW + t % 3) * XP);
+  const uint32_t gcol = (uint32_t)(wm * 32 + cq) * 2, xcol = (uint32_t)(wc * 16 + cq) * 2;
 
-  f32x4 acc[2][TAPS][CB], accb[2];
+  auto products = [&](int x0, uint32_t buf) __attribute__((always_inline)) {
+    const uint32_t xb = l0 + buf + xcol, gb = l0 + buf + xbytes + gcol;
 #pragma unroll
-  for (int ms = 0; ms < 2; ++ms) {
-    accb[ms] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < kRun / 32; ++c) {
+      uint32_t xa[2], ga[2];
 #pragma unroll
-    for (int t = 0; t < TAPS; ++t)
-#pragma unroll
-      for (int cs = 0; cs < CB; ++cs) acc[ms][t][cs] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  const bool bias = blockIdx.y == 0;
-  const bf16x8 ones = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
-
-  locate(qbeg, 0);
-  __syncthreads();
-  load(0);
-  locate(qbeg + WP, 1);
-  int buf = 1;
-  for (int q = qbeg; q < qend; q += WP) {
-    __syncthreads();  // the last patch's reads are done; the next patch is located
-#pragma unroll
-    for (int i = 0; i < XN; ++i)
-      if (xto[i] != ~0u) *reinterpret_cast<uint4 *>(lds + xto[i]) = rx[i];
-#pragma unroll
-    for (int i = 0; i < GN; ++i)
-      *reinterpret_cast<uint4 *>(lds + XBYTES + (gslot[i] * kPatch + (tid + 256 * i) / GCH % kPatch) * GP + gch[i] * 16) = rg[i];
-    __syncthreads();
-    if (q + WP < qend) {
-      load(buf);
-      buf ^= 1;
-      locate(q + 2 * WP, buf);
-    }
-    bf16x8 fa[2];
-#pragma unroll
-    for (int ms = 0; ms < 2; ++ms) fa[ms] = tr_pair(ga[0] + ms * 32, ga[1] + ms * 32);
-    if (bias) {
-#pragma unroll
-      for (int ms = 0; ms < 2; ++ms) accb[ms] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ms], ones, accb[ms], 0, 0, 0);
-    }
-#pragma unroll
-    for (int t = 0; t < TAPS; ++t)
-#pragma unroll
-      for (int cs = 0; cs < CB; ++cs) {
-        const bf16x8 fb = tr_pair(xa[0] + toff[t] + cs * 32, xa[1] + toff[t] + cs * 32);
-#pragma unroll
-        for (int ms = 0; ms < 2; ++ms)
-          acc[ms][t][cs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ms], fb, acc[ms][t][cs], 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+        const int k = 32 * c + kr + 4 * h;
+        xa[h] = xb + (uint32_t)(k + 2 * RIM * quot(x0 + k, W, a.div_w)) * XP;
+        ga[h] = gb + (uint32_t)k * GP;
       }
-  }
-  if (WP > 1) {  // the wavefronts of one channel range: their sums into wavefront wp = 0's
-    f32x4 *const red = reinterpret_cast<f32x4 *>(lds) + wm * TAPS * CB * 64 + lane;
-    for (int w = 1; w < WP; ++w) {
+      bf16x8 fa[2];
 #pragma unroll
-      for (int ms = 0; ms < 2; ++ms) {
-        __syncthreads();
-        if (wp == w) {
+      for (int ms = 0; ms < 2; ++ms) fa[ms] = tr_pair(ga[0] + ms * 32, ga[1] + ms * 32);
 #pragma unroll
-          for (int t = 0; t < TAPS; ++t)
+      for (int t = 0; t < TX; ++t) {
+        const bf16x8 fb = tr_pair(xa[0] + t * XP, xa[1] + t * XP);
 #pragma unroll
-            for (int cs = 0; cs < CB; ++cs) red[(t * CB + cs) * 64] = acc[ms][t][cs];
-        }
-        __syncthreads();
-        if (wp == 0) {
-#pragma unroll
-          for (int t = 0; t < TAPS; ++t)
-#pragma unroll
-            for (int cs = 0; cs < CB; ++cs) acc[ms][t][cs] += red[(t * CB + cs) * 64];
-        }
-        __syncthreads();
-        if (wp == w) red[0] = accb[ms];
-        __syncthreads();
-        if (wp == 0) accb[ms] += red[0];
+        for (int ms = 0; ms < 2; ++ms) acc[ms][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ms], fb, acc[ms][t], 0, 0, 0);
       }
     }
-    if (wp != 0) return;
+  };
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) load(runs[i]);
+  uint32_t buf = 0;
+  int x0 = pbeg % W;  // the column of the run's first pixel
+  for (int p0 = pbeg; p0 < pend; p0 += AHEAD * kRun) {
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      const int p = p0 + i * kRun;
+      if (p < pend) {
+        store(buf, runs[i]);
+        __syncthreads();  // this run is staged, and the other buffer's reads are done
+        load(runs[i]);
+        products(x0, buf);
+        x0 += kRun;
+        x0 -= quot(x0, W, a.div_w) * W;
+        buf = buf ? 0 : bufbytes;
+      }
+    }
   }
-  // D[m = 4 (lane / 16) + r][n = lane % 16]; a split's partials are [M][taps * Cin] and then the M bias sums
-  const int K = TAPS * Cin;
-  float *const out = a.part + (int64_t)blockIdx.z * (a.M * (int64_t)(K + 1));
+  // D[m = 4 (lane / 16) + r][n = lane % 16]
+  const int K = (TX == 3 ? 9 : 1) * Cin, c = c0 + wc * 16 + (lane & 15);
+  if (c >= Cin) return;
+  float *const out = a.part + (int64_t)split * a.M * K + c;
 #pragma unroll
   for (int ms = 0; ms < 2; ++ms)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = m0 + wm * 32 + ms * 16 + 4 * (lane >> 4) + r;
 #pragma unroll
-      for (int t = 0; t < TAPS; ++t)
-#pragma unroll
-        for (int cs = 0; cs < CB; ++cs) {
-          const int c = c0 + cs * 16 + (lane & 15);
-          if (c < Cin) out[(int64_t)m * K + t * Cin + c] = acc[ms][t][cs][r];
-        }
-      if (bias && (lane & 15) == 0) out[(int64_t)a.M * K + m] = accb[ms][r];
+      for (int t = 0; t < TX; ++t) out[(int64_t)m * K + (TX == 3 ? 3 * (dy + 1) + t : 0) * Cin] = acc[ms][t][r];
     }
 }
 
-// out[i] = sum over the splits of part[split][i], four values per lane: 16
-// wavefronts take every 16th split each, then add through LDS (a few hundred
-// splits of a small layer read one after the other left most of the GPU idle).
-__global__ void __launch_bounds__(1024) sum_splits_kernel(const float *part, int splits, int64_t n, float *out) {
-  __shared__ f32x4 red[16][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t i = ((int64_t)blockIdx.x * 64 + lane) * 4;
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (i < n)
-    for (int j = w; j < splits; j += 16) s += *reinterpret_cast<const f32x4 *>(part + (int64_t)j * n + i);
-  red[w][lane] = s;
-  __syncthreads();
-  if (w == 0 && i < n) {
+// Column sums of a bf16 matrix [P][C] (C divides 256) per kColsumPix rows: row
+// lane j of 256 / C sums rows j, j + 256 / C, ... in order, then the row lanes are
+// added in order. A lane takes two columns; two partials per block. The sums are
+// chains of up to 1024 additions, so the loads run 32 ahead of them (25 us per
+// layer on 8 x 256^2; 94 us with one load per addition).
+__global__ void __launch_bounds__(256) colsum_kernel(const uint16_t *g, int64_t P, int C, float *part) {
+  __shared__ float red[2][256];
+  const int t = threadIdx.x & 127, w = threadIdx.x >> 7, G = C / 2, lanes = 256 / C;
+  const int c = t % G * 2, j0 = t / G;
+  const int64_t blk = (int64_t)blockIdx.x * 2 + w, beg = blk * kColsumPix;
+  const int rows = (int)max((int64_t)0, min((int64_t)kColsumPix, P - beg));
+  const uint32_t *const src = reinterpret_cast<const uint32_t *>(g + beg * C + c);
+  const int step = lanes * C / 2;  // words from one of this lane's rows to the next
+  const int n = rows > j0 ? (rows - j0 + lanes - 1) / lanes : 0;
+  constexpr int U = 32;
+  uint32_t v[U], vn[U];
+  auto load = [&](int i0, uint32_t(&r)[U]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 1; k < 16; ++k) s += red[k][lane];
-    *reinterpret_cast<f32x4 *>(out + i) = s;
+    for (int u = 0; u < U; ++u) r[u] = i0 + u < n ? src[(int64_t)j0 * G + (int64_t)(i0 + u) * step] : 0u;
+  };
+  float lo = 0.f, hi = 0.f;
+  load(0, v);
+  for (int i0 = 0; i0 < n; i0 += U) {
+    load(i0 + U, vn);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u < n) {
+        lo += bf2f((uint16_t)v[u]);
+        hi += bf2f((uint16_t)(v[u] >> 16));
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = vn[u];
   }
+  red[w][j0 * C + c] = lo;
+  red[w][j0 * C + c + 1] = hi;
+  __syncthreads();
+  if (rows > 0 && j0 == 0) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      float a = 0.f;
+      for (int j = 0; j < lanes; ++j) a += red[w][j * C + c + k];
+      part[blk * C + c + k] = a;
+    }
+  }
+}
+
+// The weight gradients out[i] = sum over the splits, in order, of part[split][i]
+// (four values per lane), and in the last blocks the bias gradients outb[c] =
+// the sum in order of bsplits partials, staged in LDS 256 partials of 32 columns at a
+// time (one lane adding from memory would wait for each load).
+__global__ void __launch_bounds__(256) sum_splits_kernel(const float *part, int splits, int64_t n, float *out,
+                                                         const float *bpart, int bsplits, int nb, float *outb) {
+  __shared__ float tile[256 * 32];
+  const int64_t wblocks = (n / 4 + 255) / 256;
+  const int t = threadIdx.x;
+  if (blockIdx.x < wblocks) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + t) * 4;
+    if (i >= n) return;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 16
+    for (int j = 0; j < splits; ++j) s += *reinterpret_cast<const f32x4 *>(part + (int64_t)j * n + i);
+    *reinterpret_cast<f32x4 *>(out + i) = s;
+    return;
+  }
+  const int c0 = (int)(blockIdx.x - wblocks) * 32;
+  float s = 0.f;
+  for (int j0 = 0; j0 < bsplits; j0 += 256) {
+    const int m = min(256, bsplits - j0);
+    __syncthreads();
+    for (int e = t; e < m * 32; e += 256) tile[e] = bpart[(int64_t)(j0 + e / 32) * nb + c0 + e % 32];
+    __syncthreads();
+    if (t < 32) {
+#pragma unroll 16
+      for (int j = 0; j < m; ++j) s += tile[j * 32 + t];
+    }
+  }
+  if (t < 32) outb[c0 + t] = s;
 }
 
 // Input tensor [B][H][W][8]: solid (0/1), the scaled log Kn feature, zeros.
@@ -622,67 +703,84 @@ inline unsigned nblocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs
 
 }  // namespace
 
-hipError_t launch_conv(const ConvArgs &a, hipStream_t st) {
-  const int P = a.B * a.H * a.W;
-  const bool wide = a.nstore > 32 && a.nrows % 64 == 0;
-  if (wide) {
-    dim3 grid(nblocks(P, 128), (unsigned)((a.nstore + 63) / 64));
-    conv_kernel<64><<<grid, 256, 0, st>>>(a);
-  } else {
-    dim3 grid(nblocks(P, 128), (unsigned)((a.nstore + 31) / 32));
-    conv_kernel<32><<<grid, 256, 0, st>>>(a);
-  }
-  return hipGetLastError();
-}
-
 namespace {
-template <int TAPS, int WM, int CB>
-void wgrad_as(const WgradArgs &a, int ctiles, hipStream_t st) {
-  const dim3 grid((unsigned)(a.M / (32 * WM)), (unsigned)ctiles, (unsigned)((a.patches + a.per_split - 1) / a.per_split));
-  wgrad_kernel<TAPS, WM, CB><<<grid, 256, 0, st>>>(a);
+template <int WX, int WN, int TAPS, bool C8>
+hipError_t conv_as(ConvArgs a, hipStream_t st) {
+  // the widest tile up to 16 (8 for 64 pixels) columns that the image has use for
+  a.pw = 0;
+  while ((1 << a.pw) < std::min(a.W, WX == 1 ? 8 : 16)) ++a.pw;
+  const int PW = 1 << a.pw, PH = (64 * WX) >> a.pw, RIM = TAPS == 9 ? 1 : 0;
+  a.npx = (a.W + PW - 1) / PW;
+  a.npy = (a.H + PH - 1) / PH;
+  const int Cin = a.Ca + a.Cb, RW = PW + 2 * RIM, RR = (PH + 2 * RIM) * RW;
+  a.div_ch = (uint32_t)(((uint64_t(1) << 32) + Cin / 8 - 1) / (Cin / 8));
+  a.div_rw = (uint32_t)(((uint64_t(1) << 32) + RW - 1) / RW);
+  const size_t lds = (size_t)RR * (Cin * 2 + 16);
+  const dim3 grid((unsigned)(a.B * a.npx * a.npy), (unsigned)((a.nstore + 32 * WN - 1) / (32 * WN)));
+  conv_kernel<WX, WN, TAPS, C8><<<grid, 64 * WX * WN, lds, st>>>(a);
+  return hipGetLastError();
 }
 }  // namespace
 
-WgradPlan wgrad_plan(int M, int Ca, int Cb, int taps, int B, int H, int W) {
-  WgradPlan p;
-  // wavefronts along the output channels: as many as there are 32-channel
-  // ranges (the others split the patches); a power of two that divides M / 32
-  p.wm = M % 128 == 0 ? 4 : (M % 64 == 0 ? 2 : 1);
-  const int Cin = Ca + Cb;
-  p.cb = Ca % 32 == 0 && Cb % 32 == 0 ? 2 : 1;  // 32 input channels a block; 16 where a part has an odd 16 or 8
-  const int tiles = M / (32 * p.wm) * ((Cin + 16 * p.cb - 1) / (16 * p.cb));
-  p.max_splits = std::max(1, kWgradBlocks / tiles);
-  // patches as wide as the image up to 32 pixels (rounded up to a power of two)
-  p.pw = 0;
-  while ((1 << p.pw) < std::min(W, kPatch)) ++p.pw;
-  const int PW = 1 << p.pw, PH = kPatch >> p.pw;
-  p.npx = (W + PW - 1) / PW;
-  p.npy = (H + PH - 1) / PH;
-  p.patches = B * p.npx * p.npy;
-  const int wp = 4 / p.wm;
-  p.per_split = (p.patches + p.max_splits - 1) / p.max_splits;
-  p.per_split = (p.per_split + wp - 1) / wp * wp;
-  p.splits = (p.patches + p.per_split - 1) / p.per_split;
-  (void)taps;
-  return p;
+hipError_t launch_conv(const ConvArgs &a, hipStream_t st) {
+  const int Cin = a.Ca + a.Cb;
+  if (a.taps == 1) return a.nrows % 64 == 0 ? conv_as<2, 2, 1, false>(a, st) : conv_as<4, 1, 1, false>(a, st);
+  if (Cin == 8) return conv_as<4, 1, 9, true>(a, st);
+  // 128 output channels of 64 pixels, 64 of 128, 32 of 256: the fewest wavefronts read the same weights or pixels
+  if (a.nrows % 128 == 0) return conv_as<1, 4, 9, false>(a, st);
+  if (a.nrows % 64 == 0) return conv_as<2, 2, 9, false>(a, st);
+  return conv_as<4, 1, 9, false>(a, st);
 }
 
-hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &p, hipStream_t st) {
-  const int ct = (a.Ca + a.Cb + 16 * p.cb - 1) / (16 * p.cb);
-#define PDVM_WG(T, C)                          \
-  if (p.wm == 4) wgrad_as<T, 4, C>(a, ct, st); \
-  else if (p.wm == 2) wgrad_as<T, 2, C>(a, ct, st); \
-  else wgrad_as<T, 1, C>(a, ct, st)
-  if (a.taps == 9 && p.cb == 2) { PDVM_WG(9, 2); }
-  else if (a.taps == 9) { PDVM_WG(9, 1); }
-  else if (p.cb == 2) { PDVM_WG(1, 2); }
-  else { PDVM_WG(1, 1); }
+namespace {
+template <int TX, int WM, int WC, int XN>
+void wgrad_as(const WgradArgs &a, hipStream_t st) {
+  constexpr int BM = 32 * WM, BC = 16 * WC;
+  const int splits = (a.B * a.H * a.W + kPixPerSplit - 1) / kPixPerSplit;
+  const dim3 grid((unsigned)(a.M / BM), (unsigned)((a.Ca + a.Cb + BC - 1) / BC), (unsigned)(splits * TX));
+  const size_t lds = 2 * ((size_t)a.xrows * (BC * 2 + 16) + kRun * (BM * 2 + 16));
+  wgrad_kernel<TX, WM, WC, XN><<<grid, 64 * WM * WC, lds, st>>>(a);
+}
+// a magic reciprocal for quotients of numbers below 2^16, or 0 where they stay below 2 d
+uint32_t small_div(int d) { return d >= 512 || d == 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); }
+}  // namespace
+
+hipError_t launch_wgrad(WgradArgs a, hipStream_t st) {
+  const int rim = a.taps == 9 ? 2 : 0, W = a.W;
+  // padded pixels of a run: it spans at most (W + kRun - 2) / W + 1 rows
+  a.xrows = kRun + rim * ((W + kRun - 2) / W + 1);
+  a.div_w = small_div(W);
+  a.div_wr = small_div(W + rim);
+  // 32 input channels per block (16 where there are only 8), and 64 output channels where there are as many
+  const bool c32 = a.Ca % 32 == 0 && a.Cb % 32 == 0, wide = a.M % 64 == 0;
+  // pieces per thread: a run of a wide image, or of any (every pixel a row of its own)
+#define PDVM_WG(T, M, C)                                                                            \
+  if (a.xrows * (2 * C) <= 64 * M * C * ((140 * 2 + 64 * M - 1) / (64 * M)))                        \
+    wgrad_as<T, M, C, (140 * 2 + 64 * M - 1) / (64 * M)>(a, st);                                    \
+  else                                                                                              \
+    wgrad_as<T, M, C, (386 * 2 + 64 * M - 1) / (64 * M)>(a, st)
+  if (a.taps == 1) {
+    if (c32) { PDVM_WG(1, 1, 2); }
+    else { PDVM_WG(1, 1, 1); }
+  } else if (!c32) {
+    PDVM_WG(3, 1, 1);
+  } else if (wide) {
+    PDVM_WG(3, 2, 2);
+  } else {
+    PDVM_WG(3, 1, 2);
+  }
 #undef PDVM_WG
   return hipGetLastError();
 }
 
-hipError_t launch_sum_splits(const float *part, int splits, int64_t n, float *out, hipStream_t st) {
-  sum_splits_kernel<<<nblocks(n, 256), 1024, 0, st>>>(part, splits, n, out);
+hipError_t launch_colsum(const uint16_t *g, int64_t P, int C, float *part, hipStream_t st) {
+  colsum_kernel<<<nblocks(P, 2 * kColsumPix), 256, 0, st>>>(g, P, C, part);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_splits(const float *part, int splits, int64_t n, float *out, const float *bpart, int bsplits, int nb,
+                             float *outb, hipStream_t st) {
+  sum_splits_kernel<<<nblocks(n / 4, 256) + nblocks(nb, 32), 256, 0, st>>>(part, splits, n, out, bpart, bsplits, nb, outb);
   return hipGetLastError();
 }
 
