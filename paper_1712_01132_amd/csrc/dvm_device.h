@@ -1,4 +1,4 @@
-// Device helpers shared by the kernels of the iteration (dvm_sweep_diag.hip,
+// Device helpers shared by the kernels of the iteration (dvm_sweep_*.h,
 // dvm_sweep_rows.hip, dvm_iter.hip). Internal; not part of the C ABI.
 #pragma once
 #include <type_traits>
@@ -146,6 +146,15 @@ __device__ __forceinline__ double ramp_at(const Geo<T> &g, int64_t c) {
 template <typename T>
 __device__ __forceinline__ double ramp_step(const Geo<T> &g, int j, int p) {
   return j == 0 ? (p ? g.ramp : -g.ramp) / (double)g.n[0] : 0.0;
+}
+
+// f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N - 1>)
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
 }
 
 // Broadcast of lane V of each row of 16 lanes (DPP row_newbcast) to the row: a

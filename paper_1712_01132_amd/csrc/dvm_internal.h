@@ -218,7 +218,8 @@ struct Scratch {
   int prog_pad = kProgPad;    // ints per progress counter of the 4x4 row pipeline
 };
 
-// Kernel launchers (dvm_sweep_diag.hip, dvm_sweep_rows.hip, dvm_iter.hip).
+// Kernel launchers (dvm_sweep_{queue,diag,strips}_f{64,32}.hip, dvm_sweep_rows.hip,
+// dvm_sweep_rows4.hip, dvm_iter.hip).
 // All enqueue on `st`.
 template <typename T>
 hipError_t launch_sweep(const Batch<T> &B, int diag, hipStream_t st);

@@ -7,14 +7,6 @@
 namespace pdvm {
 namespace {
 
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (N > 0) {
-    static_for<N - 1>(f);
-    f(std::integral_constant<int, N - 1>{});
-  }
-}
-
 // The pipeline, its hand-overs, its waits and their protocols are those of
 // sweep_rows_kernel. What differs:
 //
