@@ -26,32 +26,17 @@ namespace {
 // bit 2 (MW): Maxwell walls. A voxel whose axis-j stencil meets a wall (code
 // bit 4 + j) adds a_j (1 - alpha) times its own previous-iteration value of
 // the velocity mirrored in e_j; the record's wall term is alpha rho_w.
-// h at an upstream node (x, y, z) along axis j, as upstream_fluid but without
-// the jump across the x1 wrap (the caller adds it where the value is used, so
-// nothing waits for the load early) and with no branch: the buffer, the node
-// and the velocity slot are selected (uniform values), so the load is issued
-// whatever the case and many can be in flight before the first wait.
-// The node's offset is formed in 32 bits (a problem has under 2^31 / 6
-// voxels) and scaled by the voxel's bytes colb in one 32 x 32 -> 64 bit
-// product: these are scalar instructions, a dozen per halo value fewer than
-// with 64-bit index arithmetic.
-template <typename T>
-__device__ __forceinline__ T upstream_sel(const Dom<T> &g, gptr<const T> hc, gptr<const T> hp, int j, int x, int y,
-                                          int z, int kofs, int kmir, uint32_t colb) {
-  int c[3] = {x, y, z};
-  const bool in = c[j] >= 0 && c[j] < g.n[j];
-  const Img im = image_of(j, c[j], g.n[j], g.latp);
-  c[j] = in ? c[j] : im.r;
-  const int k = (!in && im.mir) ? kmir : kofs;
-  const uint32_t cell = (uint32_t)(c[0] + g.n[0] * (c[1] + g.n[1] * c[2]));
-  const gptr<const char> b = (gptr<const char>)(in ? hc : hp) + (uint64_t)cell * colb;
-  return ((gptr<const T>)b)[k];
-}
-// The jump that upstream_sel leaves out at x1 = x (images across the wrap).
+// The jump at x1 = x (images across the wrap), added where a value is used, so
+// that nothing waits for its load early.
 template <typename T>
 __device__ __forceinline__ T wrap_jump(const Dom<T> &g, int x) {
   return (x < 0 ? T(1) : (x >= g.n[0] ? T(-1) : T(0))) * g.jump;
 }
+
+// Bits of a record's code (from R_USE1 + 2 j, R_USE2 + 2 j): the voxel's stencil along
+// axis j uses the first, the second upstream value. Below them: bit j, the first-order
+// stencil (the index of the reciprocal denominator); bit 4 + j, a Maxwell wall.
+constexpr int R_USE1 = 8, R_USE2 = 9;
 
 // LDS of one tile wavefront: the reciprocal denominators of its 64
 // velocities and the records of up to PZ planes (128 voxels in 3D).
@@ -171,22 +156,84 @@ __device__ __forceinline__ void sweep_tile(const Geo<T> &G_, int o, int grp, con
   T *const ZA = CARRY ? zc : ZAl;
   T *const ZB = CARRY ? zc + ZN : ZBl;
   const int64_t Kp = dm.Kpad;
-  const uint32_t dcol = s[0] > 0 ? colb : 0u - colb;  // bytes from one column to the next
   using lds_ptr = __attribute__((address_space(3))) const T *;
   const uint32_t rd_addr = (uint32_t)(uintptr_t)(lds_ptr)(rd_lds + lane);
   auto zof = [&](int c3) { return s[2] > 0 ? lo[2] + c3 : lo[2] + cnt[2] - 1 - c3; };
-  // the halos of plane z (the current sweep, or the images of the previous
-  // iterate outside the domain). Rows and columns past a ragged tile re-read
-  // its last one: only voxels outside the tile, which are never stored, see them.
-  auto load_halo = [&](int z, T(&L1)[TT], T(&L2)[TT], T(&B1)[TT], T(&B2)[TT]) __attribute__((always_inline)) {
+  // Values outside the tile are loaded a voxel row at a time through a buffer
+  // resource of the row (below 1 GiB, checked by the host): one scalar base per
+  // row, and per value the lane's offset. What no voxel of the plane uses (its
+  // own stencil ends at a wall or it is solid: 45 % of the halo values of the 96^3
+  // pack) gets an offset past the row's range, for which the hardware reads
+  // nothing and gives 0. The 96^3 pack's sweep took 3.48 ms with all halos
+  // loaded from 64-bit addresses formed one by one.
+  auto row_rsrc = [&](gptr<const char> base, int y, int z) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(base + (uint64_t)(uint32_t)((n1 * z + y) * n0) * colb), (short)0,
+                                             (int)(colb * (uint32_t)n0), kBufferFlags);
+  };
+  // node c along axis j: the coordinate, the buffer and the lane's offset in a
+  // voxel (the current sweep, or the image of the previous iterate outside the
+  // domain)
+  struct Node {
+    gptr<const char> base;
+    int c;
+    uint32_t k;
+  };
+  auto node_of = [&](int j, int c) __attribute__((always_inline)) {
+    const bool in = c >= 0 && c < dm.n[j];
+    const Img im = image_of(j, c, dm.n[j], dm.latp);
+    return Node{(gptr<const char>)(in ? hcc : hp), in ? c : im.r,
+                (uint32_t)((!in && im.mir) ? kmir[j] : kofs) * (uint32_t)sizeof(T)};
+  };
+  const Node nx1 = node_of(0, xs - s[0]), nx2 = node_of(0, xs - 2 * s[0]);
+  const Node ny1 = node_of(1, ys - s[1]), ny2 = node_of(1, ys - 2 * s[1]);
+  const uint32_t ox1 = nx1.k + (uint32_t)nx1.c * colb, ox2 = nx2.k + (uint32_t)nx2.c * colb;
+  // rows and columns past a ragged tile repeat its last one (never stored)
+  auto row_y = [&](int r) __attribute__((always_inline)) { return ys + min(r, cnt[1] - 1) * s[1]; };
+  uint32_t xo[TT];  // byte offset of column i in a row
 #pragma unroll
-    for (int k = 0; k < TT; ++k) {
-      const int y = ys + min(k, cnt[1] - 1) * s[1], x = xs + min(k, cnt[0] - 1) * s[0];
-      L1[k] = upstream_sel(dv, hcc, hp, 0, xs - s[0], y, z, kofs, kmir[0], colb);
-      L2[k] = upstream_sel(dv, hcc, hp, 0, xs - 2 * s[0], y, z, kofs, kmir[0], colb);
-      B1[k] = upstream_sel(dv, hcc, hp, 1, x, ys - s[1], z, kofs, kmir[1], colb);
-      B2[k] = upstream_sel(dv, hcc, hp, 1, x, ys - 2 * s[1], z, kofs, kmir[1], colb);
-    }
+  for (int i = 0; i < TT; ++i) xo[i] = (uint32_t)(xs + min(i, cnt[0] - 1) * s[0]) * colb;
+  constexpr int QN = TT / 4;
+  // the record codes of a quadrant of plane pz, lane l taking voxel l % 16
+  auto code_of = [&](int pz, int qx, int qy) __attribute__((always_inline)) {
+    return rcode[pz * NC + (4 * qy + ((lane >> 2) & 3)) * TT + 4 * qx + (lane & 3)];
+  };
+  // the halos of plane z; pz its plane in the staged records, or -1 if its
+  // records are not staged yet (everything is loaded)
+  auto load_halo = [&](int z, int pz, T(&L1)[TT], T(&L2)[TT], T(&B1)[TT], T(&B2)[TT]) __attribute__((always_inline)) {
+    static_for<QN>([&](auto Q) __attribute__((always_inline)) {
+      constexpr int q4 = 4 * Q;
+      // lane 4 r: row r's left values; lane i: column i's lower values. The nearer
+      // one is also the second upstream value of the next voxel in.
+      const uint32_t cl = code_of(max(pz, 0), 0, Q), cb = QN > 1 ? code_of(max(pz, 0), Q, 0) : cl;
+      const uint32_t cl1 = __builtin_amdgcn_mov_dpp((int)cl, 0xF5, 0xF, 0xF, true);   // quad_perm: lane + 1
+      const uint32_t cb1 = __builtin_amdgcn_mov_dpp((int)cb, 0x104, 0xF, 0xF, true);  // row_shl:4: lane + 4
+      const uint32_t all = pz < 0 ? 1u : 0u;
+      uint32_t d1 = ((((cl >> R_USE1) | (cl1 >> R_USE2)) | all) & 1u) ? 0u : kDrop;
+      uint32_t d2 = (((cl >> R_USE2) | all) & 1u) ? 0u : kDrop;
+      uint32_t e1 = ((((cb >> (R_USE1 + 2)) | (cb1 >> (R_USE2 + 2))) | all) & 1u) ? 0u : kDrop;
+      uint32_t e2 = (((cb >> (R_USE2 + 2)) | all) & 1u) ? 0u : kDrop;
+      asm volatile("s_nop 1" : "+v"(d1), "+v"(d2), "+v"(e1), "+v"(e2));
+      static_for<4>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = K;
+        const int y = row_y(q4 + k);
+        L1[q4 + k] = buffer_load<T>(row_rsrc(nx1.base, y, z), add_bcast<4 * k>(d1, ox1));
+        L2[q4 + k] = buffer_load<T>(row_rsrc(nx2.base, y, z), add_bcast<4 * k>(d2, ox2));
+        B1[q4 + k] = buffer_load<T>(row_rsrc(ny1.base, ny1.c, z), add_bcast<k>(e1, ny1.k) + xo[q4 + k]);
+        B2[q4 + k] = buffer_load<T>(row_rsrc(ny2.base, ny2.c, z), add_bcast<k>(e2, ny2.k) + xo[q4 + k]);
+      });
+    });
+  };
+  // the x3-upstream values, one and two planes back, of the 16 voxels of a
+  // quadrant of plane z: d1, d2 hold kDrop in the lanes of voxels that use none
+  auto load_z = [&](int qx, int qy, int z, uint32_t d1, uint32_t d2, T *za, T *zb) __attribute__((always_inline)) {
+    const Node nz1 = node_of(2, z - s[2]), nz2 = node_of(2, z - 2 * s[2]);
+    asm volatile("s_nop 1" : "+v"(d1), "+v"(d2));
+    static_for<16>([&](auto V) __attribute__((always_inline)) {
+      constexpr int v = V;
+      const int y = row_y(4 * qy + v / 4);
+      za[v] = buffer_load<T>(row_rsrc(nz1.base, y, nz1.c), add_bcast<v>(d1, nz1.k) + xo[4 * qx + v % 4]);
+      zb[v] = buffer_load<T>(row_rsrc(nz2.base, y, nz2.c), add_bcast<v>(d2, nz2.k) + xo[4 * qx + v % 4]);
+    });
   };
   // records of the voxels of planes c0 .. c0 + np - 1 (lane l takes voxels
   // l, l + 64, ...). The voxel's sources and wall values are loaded together
@@ -252,6 +299,7 @@ __device__ __forceinline__ void sweep_tile(const Geo<T> &G_, int o, int grp, con
         rp[6 + 3 * j] = fl ? c2 : T(0);
         rp[7 + 3 * j] = fl ? w : T(0);
         code |= (first ? 1u : 0u) << j;
+        code |= (c1 != T(0) ? 1u : 0u) << (R_USE1 + 2 * j) | (c2 != T(0) ? 1u : 0u) << (R_USE2 + 2 * j);
         if (MW && first && y1s) code |= 16u << j;
       }
       rcode[v] = fl ? code : R_SKIP;
@@ -260,22 +308,22 @@ __device__ __forceinline__ void sweep_tile(const Geo<T> &G_, int o, int grp, con
 
   const T jx1 = wrap_jump(dv, xs - s[0]), jx2 = wrap_jump(dv, xs - 2 * s[0]);  // the same for every plane
   // the tile's first plane: records, halos and (4 x 4 tiles in 3D) the two
-  // planes below, all issued before any wait
+  // planes below
   T L1[TT], L2[TT], B1[TT], B2[TT];
   stage(0, min(PZ, cnt[2]), before);
 #pragma unroll
   for (int c = 0; c < (1 << DIM); ++c) rd_lds[c * kWave + lane] = rdv[c];
-  load_halo(zof(0), L1, L2, B1, B2);
-  if (ZREG && (!CARRY || zload)) {
-    const int z = zof(0);
-#pragma unroll
-    for (int v = 0; v < (ZREG ? NC : 0); ++v) {
-      const int x = xs + min(v % TT, cnt[0] - 1) * s[0], y = ys + min(v / TT, cnt[1] - 1) * s[1];
-      ZA[v] = upstream_sel(dv, hcc, hp, 2, x, y, z - s[2], kofs, kmir[2], colb);
-      ZB[v] = upstream_sel(dv, hcc, hp, 2, x, y, z - 2 * s[2], kofs, kmir[2], colb);
+  __syncthreads();
+  load_halo(zof(0), 0, L1, L2, B1, B2);
+  if constexpr (ZREG) {
+    if (!CARRY || zload) {
+      // a value one plane back is also two planes back of the next plane's voxel
+      // (in a column, possibly the next tile's: then all are loaded)
+      const uint32_t c0 = code_of(0, 0, 0), c1 = cnt[2] > 1 ? code_of(1, 0, 0) : (CARRY ? 1u << (R_USE2 + 4) : 0u);
+      const uint32_t d1 = (((c0 >> (R_USE1 + 4)) | (c1 >> (R_USE2 + 4))) & 1u) ? 0u : kDrop;
+      load_z(0, 0, zof(0), d1, ((c0 >> (R_USE2 + 4)) & 1u) ? 0u : kDrop, ZA, ZB);
     }
   }
-  __syncthreads();
   // One 4 x 4 quadrant (qx, qy) of the tile's plane: its voxels' records go from LDS
   // to registers, lane l taking voxel l % 16, and reach the lanes of all 64
   // velocities as row_newbcast operands. Read from LDS by every lane of every
@@ -294,20 +342,14 @@ __device__ __forceinline__ void sweep_tile(const Geo<T> &G_, int o, int grp, con
     T rp[RW];
 #pragma unroll
     for (int k = 0; k < RW; ++k) rp[k] = rec[mine * RW + k];
-    const uint32_t code = rcode[mine];
+    const uint32_t code = code_of(pz, qx, qy);
     uint32_t rdo = (code & 7u) * (uint32_t)(kWave * sizeof(T)), rdrop = (code & R_SKIP) ? kDrop : 0u;
     // a DPP operand may be read two instructions after its write at the earliest
     // ("+v": the values are those of this point, not formed again after it)
     asm volatile("s_nop 1" : "+v"(rdo), "+v"(rdrop));
     T Za[ZREG || DIM == 2 ? 1 : NV], Zb[ZREG || DIM == 2 ? 1 : NV];  // 8 x 8 tiles in 3D: the x3-upstream values from h
-    if constexpr (DIM == 3 && !ZREG) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const int x = xs + min(4 * qx + v % 4, cnt[0] - 1) * s[0], y = ys + min(4 * qy + v / 4, cnt[1] - 1) * s[1];
-        Za[v] = upstream_sel(dv, hcc, hp, 2, x, y, z - s[2], kofs, kmir[2], colb);
-        Zb[v] = upstream_sel(dv, hcc, hp, 2, x, y, z - 2 * s[2], kofs, kmir[2], colb);
-      }
-    }
+    if constexpr (DIM == 3 && !ZREG)
+      load_z(qx, qy, z, ((code >> (R_USE1 + 4)) & 1u) ? 0u : kDrop, ((code >> (R_USE2 + 4)) & 1u) ? 0u : kDrop, Za, Zb);
     T num[NV], rdv[NV];
     static_for<NV>([&](auto V) __attribute__((always_inline)) {
       constexpr int v = V;
@@ -420,20 +462,15 @@ __device__ __forceinline__ void sweep_tile(const Geo<T> &G_, int o, int grp, con
     // the next plane's halos, issued before this plane's stores: waiting for
     // them then does not wait for the stores
     T L1n[TT], L2n[TT], B1n[TT], B2n[TT];
-    if (DIM == 3 && NEXT) load_halo(zof(min(c3 + 1, cnt[2] - 1)), L1n, L2n, B1n, B2n);
-    // stores: one buffer resource per row of the tile (a row of h spans below
-    // 1 GiB, checked by the host)
-    __amdgpu_buffer_rsrc_t rowrs[TT];
+    if (DIM == 3 && NEXT) load_halo(zof(min(c3 + 1, cnt[2] - 1)), pz + 1 < PZ ? pz + 1 : -1, L1n, L2n, B1n, B2n);
+    __amdgpu_buffer_rsrc_t rowrs[TT];  // stores
     uint32_t vx[TT];  // this lane's byte offset of column k in a row
 #pragma unroll
     for (int k = 0; k < TT; ++k) {
-      rowrs[k] = __builtin_amdgcn_make_buffer_rsrc(
-          (void *)((gptr<char>)hc + (uint64_t)(uint32_t)((n1 * z + ys + min(k, cnt[1] - 1) * s[1]) * n0) * colb),
-          (short)0, (int)(colb * (uint32_t)n0), kBufferFlags);
-      vx[k] = kst + (uint32_t)xs * colb + (uint32_t)k * dcol;
+      rowrs[k] = row_rsrc((gptr<const char>)hcc, row_y(k), z);
+      vx[k] = kst + xo[k];
     }
     // the quadrants in sweep order (one for 4 x 4 tiles)
-    constexpr int QN = TT / 4;
     T top1[QN > 1 ? TT : 1], top2[QN > 1 ? TT : 1];  // the lower quadrants' top two rows
     static_for<QN>([&](auto QY) __attribute__((always_inline)) {
       T La[4], Lb[4], N[NV];
