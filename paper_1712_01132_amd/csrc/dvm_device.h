@@ -139,9 +139,12 @@ __device__ __forceinline__ T wall_at_y1(const Dom<T> &g, PW wall, int j, int s, 
 // the upstream node y1 of the wall value (axis j, half p) that x stores: half 1
 // serves the sweep along +e_j (y1 = x - e_j), half 0 the sweep along -e_j.
 template <typename T>
-__device__ __forceinline__ double ramp_at(const Geo<T> &g, int64_t c) {
-  const int x = (int)(c % g.n[0]);
+__device__ __forceinline__ double ramp_x(const Geo<T> &g, int x) {
   return g.ramp * (0.5 - (x + 0.5) / (double)g.n[0]);
+}
+template <typename T>
+__device__ __forceinline__ double ramp_at(const Geo<T> &g, int64_t c) {
+  return ramp_x(g, (int)(c % g.n[0]));
 }
 template <typename T>
 __device__ __forceinline__ double ramp_step(const Geo<T> &g, int j, int p) {

@@ -438,28 +438,85 @@ __global__ void init_moments_kernel(Geo<T> g, const double *rho, const double *u
   }
 }
 
+// The local equilibrium as start distribution. Bound by its stores (all of h once):
+// a thread owns 16 bytes of adjacent slots of a voxel, whose octant and
+// velocities it works out once, and takes every nt-th voxel; the values of
+// kInitAhead voxels are loaded before the first is needed. (One slot per
+// thread, its voxel, octant and velocity from two 64-bit divisions each time:
+// 8.5 ms on 96^3 voxels of 4096 velocities in FP32, 14.5 GB, now 4.1 ms.)
+constexpr int kInitAhead = 4, kInitBlock = 256, kInitBlocks = 2048;
 template <typename T, int DIM>
-__global__ void init_h_kernel(Geo<T> g, const double *rho, const double *u) {
+__global__ void __launch_bounds__(kInitBlock) init_h_kernel(Geo<T> g, const double *rho, const double *u) {
+  constexpr int VEC = 16 / (int)sizeof(T);  // divides Ko_pad: a chunk stays in one octant
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
   const int par = g.ctl->par;
-  const int64_t total = g.N * g.Kpad;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t c = e / g.Kpad;
-    const int k = (int)(e - c * g.Kpad);
-    const int o = k / g.Ko_pad, q = k - o * g.Ko_pad;
-    double v = 0.0;  // psi of the local equilibrium is tau / 2 = 0
-    if (q < g.Ko && g.phm[q] != T(0) && !(g.flags[c] & F_SOLID)) {
-      v = (rho ? rho[c] : 0.0) - (g.dev ? ramp_at(g, c) : 0.0);  // offset form: h - rho_r
-      if (u)
-        for (int j = 0; j < DIM; ++j) {
-          const double vj = ((o >> j) & 1) ? -(double)g.absv[j * g.Ko_pad + q] : (double)g.absv[j * g.Ko_pad + q];
-          v += 2.0 * u[j * g.N + c] * vj;
-        }
+  const uint32_t nchunk = (uint32_t)(g.Kpad / VEC), t = blockIdx.x * (uint32_t)kInitBlock + threadIdx.x;
+  const uint32_t nt = gridDim.x * (uint32_t)kInitBlock / nchunk, c0 = t / nchunk;  // voxels at a time, the thread's first
+  if (c0 >= nt) return;
+  const int k = (int)(t - c0 * nchunk) * VEC, o = k / g.Ko_pad, q = k - o * g.Ko_pad;
+  double vj[VEC][DIM];
+  bool live[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    live[i] = q + i < g.Ko && g.phm[q + i] != T(0);  // psi of the local equilibrium is tau / 2 = 0
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      const double a = live[i] ? (double)g.absv[j * g.Ko_pad + q + i] : 0.0;
+      vj[i][j] = ((o >> j) & 1) ? -a : a;
     }
-    g.h[par][e] = T(v);
   }
+  T *const h = g.h[par] + k;
+  const uint32_t n0 = (uint32_t)g.n[0];
+  struct Fields {
+    uint32_t f[kInitAhead];
+    double r[kInitAhead], u[kInitAhead][DIM];
+  };
+  auto load = [&](int64_t cb, Fields &v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < kInitAhead; ++a) {
+      const int64_t c = min(cb + (int64_t)a * nt, g.N - 1);
+      v.f[a] = g.flags[c];
+      v.r[a] = rho ? rho[c] : 0.0;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) v.u[a][j] = u ? u[j * g.N + c] : 0.0;
+    }
+  };
+  auto store = [&](int64_t c, const Fields &w, int a) __attribute__((always_inline)) {
+    const double base = w.r[a] - (g.dev ? ramp_x(g, (int)((uint32_t)c % n0)) : 0.0);  // offset form: h - rho_r
+    vec_t out;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      double v = base;
+      if (u) {
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) v += 2.0 * w.u[a][j] * vj[i][j];
+      }
+      out[i] = live[i] && !(w.f[a] & F_SOLID) ? T(v) : T(0);
+    }
+    *(vec_t *)(h + c * g.Kpad) = out;
+  };
+  // the next voxels' fields are loaded before these voxels' stores: a wait for
+  // them then does not wait for the stores
+  Fields cur, next;
+  load(c0, cur);
+  int64_t cb = c0;
+  const int64_t step = (int64_t)kInitAhead * nt;
+  for (; cb + (kInitAhead - 1) * (int64_t)nt < g.N; cb += step) {
+    load(cb + step, next);
+#pragma unroll
+    for (int a = 0; a < kInitAhead; ++a) store(cb + (int64_t)a * nt, cur, a);
+    cur = next;
+  }
+#pragma unroll
+  for (int a = 0; a < kInitAhead; ++a)
+    if (cb + (int64_t)a * nt < g.N) store(cb + (int64_t)a * nt, cur, a);
 }
 
-// Temperature and heat-flux diagnostics from the stored distribution.
+// Temperature and heat-flux diagnostics from the stored distribution, a
+// wavefront per voxel. Bound by reading h: the octants' values of a velocity
+// are loaded together and share its weights. (Octant by octant, each value
+// waiting for its own weights: 3.4 ms on 96^3 voxels of 4096 velocities in FP32,
+// 5 GB of fluid, now 1.18 ms.)
 template <typename T, int DIM>
 __global__ void __launch_bounds__(kMomBlock) diagnostics_kernel(Geo<T> g, double *tau, double *qf) {
   const int par = g.ctl->par;
@@ -475,28 +532,35 @@ __global__ void __launch_bounds__(kMomBlock) diagnostics_kernel(Geo<T> g, double
       continue;
     }
     double e = 0, r = 0, qq[3] = {0, 0, 0};
-    for (int o = 0; o < (1 << DIM); ++o)
-      for (int q = lane; q < g.Ko; q += kWave) {
-        const double hv = (double)h[c * g.Kpad + o * g.Ko_pad + q];
-        double vsq = DIM == 2 ? 0.5 : 0.0;
-        double vj[3];
-        for (int j = 0; j < DIM; ++j) {
-          const double a = (double)g.absv[j * g.Ko_pad + q];
-          vj[j] = ((o >> j) & 1) ? -a : a;
-          vsq += a * a;
-        }
-        if (g.psi && g.phm[q] == T(0)) {
-          // psi = int (v3^2 - 1/2) h: the energy takes W psi, q_j takes W v_j psi
-          const double w = g.wq[(1 + DIM) * g.Ko_pad + q];
-          e += w * hv;
-          for (int j = 0; j < DIM; ++j) qq[j] += w * vj[j] * hv;
-          continue;
-        }
-        const double w = g.wq[q];
-        r += w * hv;
-        e += w * vsq * hv;
-        for (int j = 0; j < DIM; ++j) qq[j] += w * vj[j] * (vsq - 2.5) * hv;
+#pragma unroll 2
+    for (int q = lane; q < g.Ko; q += kWave) {
+      T hv[1 << DIM];
+#pragma unroll
+      for (int o = 0; o < (1 << DIM); ++o) hv[o] = h[c * g.Kpad + o * g.Ko_pad + q];
+      // psi = int (v3^2 - 1/2) h: the energy takes W psi, q_j takes W v_j psi
+      const bool ps = g.psi && g.phm[q] == T(0);
+      double vsq = DIM == 2 ? 0.5 : 0.0, a[DIM];
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) {
+        a[j] = (double)g.absv[j * g.Ko_pad + q];
+        vsq += a[j] * a[j];
       }
+      const double w = g.wq[(ps ? (1 + DIM) * g.Ko_pad : 0) + q];
+      double s = 0, sj[DIM];
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) sj[j] = 0;
+#pragma unroll
+      for (int o = 0; o < (1 << DIM); ++o) {
+        const double x = (double)hv[o];
+        s += x;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) sj[j] += ((o >> j) & 1) ? -x : x;
+      }
+      r += ps ? 0.0 : w * s;
+      e += ps ? w * s : w * vsq * s;
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) qq[j] += w * a[j] * (ps ? 1.0 : vsq - 2.5) * sj[j];
+    }
     r = wave_sum(r);
     e = wave_sum(e);
     if (g.dev) {  // offset form: the moments of rho_r
@@ -636,13 +700,17 @@ hipError_t launch_arm(const Batch<T> &B, double tol, int mode, int64_t max_iters
 
 template <typename T>
 hipError_t launch_init_state(const Geo<T> &g, const double *rho, const double *u, hipStream_t st) {
-  const int gm = grid_for(g.N, 256), gh = grid_for(g.N * g.Kpad, 256);
+  // the start distribution: threads to fill the chip, at least one voxel's chunks
+  const int64_t nchunk = g.Kpad / (16 / (int64_t)sizeof(T));
+  const int gm = grid_for(g.N, 256);
+  const int gh = (int)std::max<int64_t>(grid_for(nchunk, kInitBlock),
+                                        std::min<int64_t>(grid_for(g.N * nchunk, kInitBlock), kInitBlocks));
   if (g.dim == 2) {
     hipLaunchKernelGGL((init_moments_kernel<T, 2>), dim3(gm), dim3(256), 0, st, g, rho, u);
-    hipLaunchKernelGGL((init_h_kernel<T, 2>), dim3(gh), dim3(256), 0, st, g, rho, u);
+    hipLaunchKernelGGL((init_h_kernel<T, 2>), dim3(gh), dim3(kInitBlock), 0, st, g, rho, u);
   } else {
     hipLaunchKernelGGL((init_moments_kernel<T, 3>), dim3(gm), dim3(256), 0, st, g, rho, u);
-    hipLaunchKernelGGL((init_h_kernel<T, 3>), dim3(gh), dim3(256), 0, st, g, rho, u);
+    hipLaunchKernelGGL((init_h_kernel<T, 3>), dim3(gh), dim3(kInitBlock), 0, st, g, rho, u);
   }
   return hipGetLastError();
 }
