@@ -228,11 +228,11 @@ hipError_t launch_sweep(const Batch<T> &B, int diag, hipStream_t st);
 // chain's bands run on one XCD (checked with launch_xcd_probe).
 template <typename T>
 hipError_t launch_sweep_rows(const Batch<T> &B, bool local, hipStream_t st, const Scratch &scr = Scratch{});
-// The same with 4 x 4 tiles, stencil rule 1 and diffuse walls (every collision
+// The same with 4 x 4 tiles and stencil rule 1 (every collision and wall
 // model), as launch_sweep_rows forwards it; blocks of rows4_threads threads.
 template <typename T>
 bool uses_rows4(const Batch<T> &B) {
-  return B.tile_edge == 4 && !B.y2wall && !B.maxwell;
+  return B.tile_edge == 4 && !B.y2wall;
 }
 constexpr int rows4_threads() { return kWave * (band_waves(4) + 1); }
 template <typename T>

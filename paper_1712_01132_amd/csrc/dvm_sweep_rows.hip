@@ -524,8 +524,7 @@ void launch_rows_local(const Batch<T> &B, dim3 grid, hipStream_t st, const Scrat
   else if (B.tau_fb) PDVM_ROWS(TTV, false, 5);                   \
   else PDVM_ROWS(TTV, false, 4)
   if (B.tile_edge == 4) {
-    if (B.maxwell) { PDVM_ROWS_MW(4); }
-    else { PDVM_ROWS_EXT(4, true); }  // stencil rule 1: sweep_rows4_kernel
+    PDVM_ROWS_EXT(4, true);  // stencil rule 1: sweep_rows4_kernel
   } else {
     if (B.maxwell) { PDVM_ROWS_MW(8); }
     else if (B.y2wall) { PDVM_ROWS_EXT(8, true); }

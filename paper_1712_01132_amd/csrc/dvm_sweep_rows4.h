@@ -51,15 +51,16 @@ namespace {
 // Measured (MI355X, sweep per iteration, this kernel against sweep_rows_kernel
 // with 4 x 4 tiles): 512^2 rock with 32 x 32 velocities FP64 0.66 -> 0.44 ms,
 // FP32 0.53 -> 0.31 ms; 540^2 image with 8 x 8 velocities FP64 0.66 -> 0.40 ms;
-// 64^2 cell with 16 x 16 velocities FP64 70 -> 49 us.
+// 64^2 cell with 16 x 16 velocities FP64 70 -> 49 us, 203 x 157 with 16 x 16
+// velocities, tau, Shakhov and Maxwell walls FP64 414 -> 242 us (one branch and one
+// load after the other per voxel at a wall, against one round trip per axis of a tile).
 template <typename T, bool LOCAL, int NW, int EXT>
 __global__ void __launch_bounds__(kWave * (NW + 1))
     sweep_rows4_kernel(const Geo<T> *__restrict__ G, const int *__restrict__ row_off, int nprob, int stride,
                        int32_t *__restrict__ prog_scr, int pad, uint8_t *__restrict__ xcc_scr) {
   constexpr int DIM = 2, TT = 4, NC = 16;
   constexpr int RING = 2, RING_IN = 4;  // slots of each hand-over: from the row below, from the importer
-  constexpr bool TAU = (EXT & 1) != 0, SH = (EXT & 2) != 0;
-  static_assert((EXT & 4) == 0, "Maxwell walls: sweep_rows_kernel");
+  constexpr bool TAU = (EXT & 1) != 0, SH = (EXT & 2) != 0, MW = (EXT & 4) != 0;
   constexpr uint32_t kDrop = 0x40000000u;  // past any row's range; a sum of two does not wrap
   __shared__ T rd_lds[4 * kWave];
   // wavefront w reads its bottom halo from slot a of ring_of(w)
@@ -110,7 +111,8 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   const T ph = TAU ? as_global(G_.phm)[qq] : T(1);
   Dom<T> dv = dm;
   if (TAU) dv.jump = dm.jump * ph;
-  T vv[2], aa[2], cq[2] = {T(0), T(0)};
+  T vv[2], aa[2], cq[2] = {T(0), T(0)}, am[2] = {T(0), T(0)};
+  const T spec = G_.spec, alpha = G_.alpha;
   const T qs = SH ? as_global(G_.qsf)[qq] : T(0);
 #pragma unroll
   for (int k = 0; k < DIM; ++k) {
@@ -119,6 +121,7 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
     vv[k] = s[k] > 0 ? av : -av;
     aa[k] = as_global(G_.av)[k * Ko_pad + qq];
     if (SH) cq[k] = (s[k] > 0 ? a : -a) * qs;
+    if (MW) am[k] = aa[k] * spec;
   }
   const T vsqm = TAU ? as_global(G_.vsqm)[qq] : T(0);
   if (w == 0) {
@@ -314,12 +317,16 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   // that nothing reads and that is not stored.
   T rs[3], rc1[2], rc2[2], rw[2], rt = T(0), rq[2] = {T(0), T(0)};
   uint32_t rdo, rdrop;
+  // MW: per axis, 0 for a voxel whose stencil meets a wall, else past the row's range
+  uint32_t rm[2] = {kDrop, kDrop};
+  bool walls = false;  // MW: some voxel's does
   bool live = true;  // the tile holds fluid (or is one row thick: it hands on the row below)
   auto build = [&](const Raw &R, int a) __attribute__((always_inline)) {
     int cnt0;
     xs_of(a, cnt0);
     const bool fl = vi < cnt0 && vrow && !(R.f & F_SOLID);
     uint32_t code = 0;
+    walls = false;
 #pragma unroll
     for (int k = 0; k < 3; ++k) rs[k] = reg_copy(R.sv[k]);
     if (TAU) rt = reg_copy(R.svt);
@@ -333,7 +340,12 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
       const bool first = fj & 1u, y1s = fj & 2u;
       rc1[k] = fl ? (first ? (y1s ? T(0) : T(1)) : T(2)) : T(0);
       rc2[k] = fl && !first ? T(-0.5) : T(0);
-      rw[k] = fl && first && y1s ? R.wv[k] : T(0);
+      const bool at_wall = fl && first && y1s;
+      rw[k] = at_wall ? (MW ? alpha * R.wv[k] : R.wv[k]) : T(0);
+      if (MW) {
+        rm[k] = at_wall ? 0u : kDrop;
+        walls = walls || __ballot(at_wall) != 0;
+      }
       code |= (first ? 1u : 0u) << k;
     }
     rdo = fl ? code * (uint32_t)(kWave * sizeof(T)) : 0u;
@@ -344,6 +356,7 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
                  "v"(rw[0]), "v"(rw[1]), "v"(rdo), "v"(rdrop));
     if (TAU) asm volatile("s_nop 1" ::"v"(rt));
     if (SH) asm volatile("s_nop 1" ::"v"(rq[0]), "v"(rq[1]));
+    if (MW) asm volatile("s_nop 1" ::"v"(rm[0]), "v"(rm[1]));
   };
   T L1[TT], L2[TT];  // left halo: previous tile's last two columns, or images across the x1 wrap
 #pragma unroll
@@ -384,10 +397,13 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
     if (live) {
       // --- what does not depend on the halo: the sources and the denominators ----
       T num[NC], rdv[NC];
-      static_for<NC>([&](auto V) __attribute__((always_inline)) {
-        constexpr int v = V;
-        rdv[v] = *(lds_ptr)(uintptr_t)add_bcast<v>(rdo, rd_addr);
-      });
+      auto read_rd = [&]() __attribute__((always_inline)) {
+        static_for<NC>([&](auto V) __attribute__((always_inline)) {
+          constexpr int v = V;
+          rdv[v] = *(lds_ptr)(uintptr_t)add_bcast<v>(rdo, rd_addr);
+        });
+      };
+      if (!MW) read_rd();
       static_for<NC>([&](auto V) __attribute__((always_inline)) {
         constexpr int v = V;
         T x = bcast<v>(rs[0]);
@@ -401,6 +417,33 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
         }
         num[v] = x;
       });
+      if constexpr (MW) {
+        // a voxel at a wall along axis k: a_k (1 - alpha) times its own previous
+        // iterate at the velocity mirrored in e_k. The loads of the tile's voxels go
+        // together (those of voxels at no wall are dropped and give 0), one
+        // round trip per axis of a tile that meets walls
+        if (walls) {
+          const gptr<char> hpb = (gptr<char>)(gptr<T>)(T *)G_.hprev;
+          static_for<2>([&](auto K) __attribute__((always_inline)) {
+            constexpr int k = K;
+            const uint32_t at = (uint32_t)kmir[k] * (uint32_t)sizeof(T) + (uint32_t)xs * colb;
+            T hm[NC];
+            static_for<NC>([&](auto V) __attribute__((always_inline)) {
+              constexpr int v = V;
+              hm[v] = buffer_load<T>(
+                  __builtin_amdgcn_make_buffer_rsrc(
+                      (void *)(hpb + (uint64_t)(uint32_t)((ys + min(v / TT, cnt1 - 1) * s[1]) * n0) * colb), (short)0,
+                      (int)(colb * (uint32_t)n0), kBufferFlags),
+                  add_bcast<v>(rm[k], at + (uint32_t)(v % TT) * dcol));
+            });
+            static_for<NC>([&](auto V) __attribute__((always_inline)) {
+              constexpr int v = V;
+              num[v] = fma(am[k], hm[v], num[v]);
+            });
+          });
+        }
+      }
+      if (MW) read_rd();  // registers: after the walls' loads
       // --- bottom halo ------------------------------------------------------------
       T B2[TT];
       {

@@ -8,8 +8,12 @@ void launch_rows4_local(const Batch<T> &B, dim3 grid, hipStream_t st, const Scra
 #define PDVM_ROWS4(E)                                                                               \
   hipLaunchKernelGGL((sweep_rows4_kernel<T, LOCAL, band_waves(4), E>), grid, dim3(rows4_threads()), 0, st, B.d_geo, \
                      B.d_row_off, B.nprob, B.row_stride, scr.progress, scr.prog_pad, scr.xcc)
-  // EXT: bit 0 tau fed back (psi), bit 1 Shakhov
-  if (B.shakhov) PDVM_ROWS4(3);
+  // EXT: bit 0 tau fed back (psi), bit 1 Shakhov, bit 2 Maxwell walls
+  if (B.maxwell) {
+    if (B.shakhov) PDVM_ROWS4(7);
+    else if (B.tau_fb) PDVM_ROWS4(5);
+    else PDVM_ROWS4(4);
+  } else if (B.shakhov) PDVM_ROWS4(3);
   else if (B.tau_fb) PDVM_ROWS4(1);
   else PDVM_ROWS4(0);
 #undef PDVM_ROWS4

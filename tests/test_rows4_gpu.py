@@ -91,3 +91,17 @@ def test_channel_without_solid_tiles():
     b = _run(mask, "diagonals", 20, tile=[8, 8])
     for x, y in zip(a[1], b[1]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n1,n2,tile", [(2, 3, [4, 4]), (9, 65, [4, 4]), (40, 95, [4, 4]), (33, 37, [3, 1]), (131, 66, [2, 3])])
+@pytest.mark.parametrize("kw", [dict(), dict(tau_feedback=True), dict(tau_feedback=True, prandtl=2 / 3),
+                                dict(lateral="periodic")])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_maxwell_walls_equal_the_tile_diagonals(n1, n2, tile, kw, precision):
+    """Tiles with walls along one axis, both or none, ragged and thin tiles."""
+    mask = _mask(n1, n2, n1 + n2)
+    for schedule in ("rows", "rows-agent"):
+        a = _run(mask, schedule, 12, tile=tile, precision=precision, nv=[8, 12], accommodation=0.7, **kw)
+        b = _run(mask, "diagonals", 12, tile=[4, 4], precision=precision, nv=[8, 12], accommodation=0.7, **kw)
+        for x, y in zip(a[1], b[1]):
+            assert np.array_equal(x, y)
