@@ -197,6 +197,16 @@ int forward(pdvm_unet *n, const Slots &sl, int B) {
 int backward(pdvm_unet *n, int B) {
   hipStream_t st = n->stream;
   int cur = 0;
+  WtBackArgs wb{};  // layer 0 has no input gradient
+  wb.wt = n->wbf;
+  wb.wb = n->wback;
+  for (int l = 1; l < kLayers; ++l) {
+    wb.off[wb.layers] = n->offw[l];
+    wb.Cout[wb.layers] = rows_of(l);
+    wb.Cin[wb.layers] = cin_of(l);
+    wb.taps[wb.layers++] = kLayer[l].taps;
+  }
+  UCHK(n, launch_wt_back(wb, st));
   for (int l = kLayers - 1; l >= 0; --l) {
     const LayerDef &L = kLayer[l];
     const int lev = level_of(l);
@@ -228,13 +238,12 @@ int backward(pdvm_unet *n, int B) {
     UCHK(n, launch_sum_splits(n->part, splits, nw, n->grads + n->offw[l], n->bpart, bsplits, rows, n->grads + n->offb[l], st));
     if (l == 0) break;
     // input gradient: a convolution of the output gradient with the flipped, transposed weights
-    UCHK(n, launch_wt_back(n->wbf + n->offw[l], rows, cin, L.taps, n->wback, st));
     const int pin = L.in_a;
     const bool cat = L.in_b >= 0, pooled = pin == P1 || pin == P2 || pin == P3;
     ConvArgs a{};
     a.xa = g;
     a.Ca = rows;
-    a.wt = n->wback;
+    a.wt = n->wback + n->offw[l];
     a.nrows = cin;
     a.taps = L.taps;
     a.B = B;
@@ -364,8 +373,6 @@ int pdvm_unet_create(int32_t n1, int32_t n2, int32_t batch_max, int32_t dataset_
     o += rows_of(l);
   }
   n->np = o;
-  int64_t wback_max = 0;
-  for (int l = 1; l < kLayers; ++l) wback_max = std::max(wback_max, (int64_t)rows_of(l) * kLayer[l].taps * cin_of(l));
   // partial buffers for the weight and bias gradients
   for (int l = 0; l < kLayers; ++l) {
     const int64_t P = n->pix(batch_max, level_of(l));
@@ -382,7 +389,7 @@ int pdvm_unet_create(int32_t n1, int32_t n2, int32_t batch_max, int32_t dataset_
   add((void **)&n->adam_m, sizeof(float) * n->np);
   add((void **)&n->adam_v, sizeof(float) * n->np);
   add((void **)&n->wbf, 2 * n->np);
-  add((void **)&n->wback, 2 * wback_max);
+  add((void **)&n->wback, 2 * n->np);
   for (int a = 0; a < NACT; ++a) {
     const size_t cnt = (size_t)n->pix(batch_max, kAct[a].level) * kAct[a].ch;
     add((void **)&n->act[a], 2 * cnt);

@@ -78,7 +78,18 @@ hipError_t launch_loss(const float *pred, const uint8_t *solid_set, const float 
 hipError_t launch_adam(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t st);
 hipError_t launch_to_bf16(const float *src, int64_t n, uint16_t *dst, hipStream_t st);
-hipError_t launch_wt_back(const uint16_t *wt, int Cout, int Cin, int taps, uint16_t *wb, hipStream_t st);
+// The weights of every input-gradient convolution (nothing for layer 0's), one
+// launch: layer l's from wt + off[l] to wb + off[l].
+struct WtBackArgs {
+  static constexpr int kMax = 16;
+  const uint16_t *wt;
+  uint16_t *wb;
+  int layers;
+  int64_t off[kMax];
+  int Cout[kMax], Cin[kMax], taps[kMax];
+  int first[kMax + 1];  // set by the launch: each layer's first block
+};
+hipError_t launch_wt_back(WtBackArgs a, hipStream_t st);
 hipError_t launch_targets(const uint8_t *solid, const double *rho, const double *u, int H, int W, double jump,
                           double kn256, float *target, float *wsamp_one, hipStream_t st);
 hipError_t launch_fields(const float *pred, const uint8_t *solid, int H, int W, double jump, double kn256,

@@ -653,13 +653,18 @@ __global__ void to_bf16_kernel(const float *src, int64_t n, uint16_t *dst) {
 }
 
 // Weights of the input-gradient convolution: wb[c][t * Cout + o] = wt[o][(taps-1-t) * Cin + c].
-__global__ void wt_back_kernel(const uint16_t *wt, int Cout, int Cin, int taps, uint16_t *wb) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)Cout * Cin * taps) return;
-  const int o = (int)(i % Cout);
-  int64_t r = i / Cout;
-  const int t = (int)(r % taps);
-  const int c = (int)(r / taps);
+// All layers in one launch (each is a few us of latency, and so was its launch:
+// 14 of 4.7 us a step, now one of 11 us).
+__global__ void __launch_bounds__(256) wt_back_kernel(WtBackArgs a) {
+  int l = 0;
+  while (l + 1 < a.layers && (int)blockIdx.x >= a.first[l + 1]) ++l;
+  const int Cout = a.Cout[l], Cin = a.Cin[l], taps = a.taps[l];
+  const uint16_t *const wt = a.wt + a.off[l];
+  uint16_t *const wb = a.wb + a.off[l];
+  const int i = ((int)blockIdx.x - a.first[l]) * 256 + (int)threadIdx.x;
+  if (i >= Cout * Cin * taps) return;
+  const int o = i % Cout, r = i / Cout;
+  const int t = r % taps, c = r / taps;
   wb[i] = wt[(int64_t)o * taps * Cin + (int64_t)(taps - 1 - t) * Cin + c];
 }
 
@@ -852,8 +857,12 @@ hipError_t launch_to_bf16(const float *src, int64_t n, uint16_t *dst, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_wt_back(const uint16_t *wt, int Cout, int Cin, int taps, uint16_t *wb, hipStream_t st) {
-  wt_back_kernel<<<nblocks((int64_t)Cout * Cin * taps, 256), 256, 0, st>>>(wt, Cout, Cin, taps, wb);
+hipError_t launch_wt_back(WtBackArgs a, hipStream_t st) {
+  if (a.layers < 1 || a.layers > WtBackArgs::kMax) return hipErrorInvalidValue;
+  a.first[0] = 0;
+  for (int l = 0; l < a.layers; ++l)
+    a.first[l + 1] = a.first[l] + (int)(((int64_t)a.Cout[l] * a.Cin[l] * a.taps[l] + 255) / 256);
+  wt_back_kernel<<<a.first[a.layers], 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
