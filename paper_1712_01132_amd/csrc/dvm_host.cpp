@@ -258,6 +258,9 @@ uint64_t fnv1a(uint64_t h, const void *data, size_t n) {
   return h;
 }
 
+// Blocks of the moment kernel at 16 fluid voxels per wavefront.
+int64_t moment_blocks16(int64_t fluid) { return std::max<int64_t>(1, std::min<int64_t>((fluid + 63) / 64, 1024)); }
+
 int validate_and_build(const pdvm_config *cfg, Problem &P, std::string &err) {
   if (!cfg) { err = "config is NULL"; return PDVM_E_INVAL; }
   if (cfg->dim != 2 && cfg->dim != 3) { err = "dim must be 2 or 3"; return PDVM_E_INVAL; }
@@ -522,8 +525,7 @@ int validate_and_build(const pdvm_config *cfg, Problem &P, std::string &err) {
   // 2 voxels each. With 16 per wavefront a 64 x 64 cell took 24 us, a wavefront
   // walking its voxels one latency after the other; now 7.2 us. (Down to 2 up to
   // the full round, a batch of 64 mid-sized problems took 1.33 instead of 1.19 ms.)
-  P.mom_blocks = (int)std::max<int64_t>(
-      1, std::min<int64_t>(std::max<int64_t>((P.fluid + 63) / 64, std::min<int64_t>((P.fluid + 7) / 8, 256)), 1024));
+  P.mom_blocks = (int)std::max<int64_t>(moment_blocks16(P.fluid), std::min<int64_t>((P.fluid + 7) / 8, 256));
   uint64_t fp = 1469598103934665603ull;
   const double scal[7] = {P.kn, P.jump, (double)P.lateral_periodic, (double)P.tau_fb, (double)P.stencil_rule, P.prandtl,
                           P.spec};
@@ -670,6 +672,7 @@ struct pdvm_solver {
   hipError_t scratch_err = hipSuccess;
   size_t scr_part = 0, scr_prog = 0, scr_xcc = 0, scr_qctr = 0, scr_qflags = 0, scr_need = 0;
   int scr_pad = 1;                 // ints per row-pipeline counter there
+  bool scr_own_part = false;       // the moments' partials do not fit there: the problems' own are used
   std::vector<int64_t> start_iters;
   hipGraphExec_t graph = nullptr;
   int graph_iters = 0;
@@ -1415,18 +1418,28 @@ int create_common(const pdvm_config *cfgs, int n, void *dev_workspace, size_t ws
     s->scratch_err = hipGetDevice(&dev);
     if (s->scratch_err == hipSuccess) s->scratch_err = scratch_address(dev, &ptr);
     s->scratch_dev = (char *)ptr;
-    s->scr_part = 0;
-    s->scr_prog = align256((size_t)s->h_blk_off[n] * 4 * sizeof(double));
     const size_t pipe = (size_t)std::max(s->h_row_off[n], s->h_strip_off[n]);
     const bool rows4 = s->rows && (s->precision == PDVM_FP64 ? uses_rows4(s->bd) : uses_rows4(s->bf));
-    for (int pad : {rows4 ? kProgPad : 1, 1}) {  // padded counters where they fit
+    auto lay_out = [&](size_t partials, int pad) {
+      s->scr_part = 0;
       s->scr_pad = pad;
+      s->scr_prog = align256(partials * 4 * sizeof(double));
       s->scr_xcc = s->scr_prog + align256(pipe * sizeof(int32_t) * pad);
       s->scr_qctr = s->scr_xcc + align256(pipe);
       s->scr_qflags = s->scr_qctr + (s->queue ? align256(kQueueCounterInts * 4) : 0);
-      s->scr_need = s->scr_qflags + (s->queue ? align256(s->qflag_ints * 4) : 0);
-      if (s->scr_need <= kNoAllocScratchBytes) break;
-    }
+      return s->scr_qflags + (s->queue ? align256(s->qflag_ints * 4) : 0);
+    };
+    // the need held against the limit counts 16 voxels per wavefront in the
+    // moments and plain counters. Beyond it, as far as it fits: the counters on
+    // lines of their own, the partials of small problems' further wavefronts;
+    // where those do not fit, the problems' own partials serve.
+    size_t partials16 = 0;
+    for (const Problem &P : s->P) partials16 += (size_t)moment_blocks16(P.fluid);
+    s->scr_need = lay_out(partials16, 1);
+    const size_t partials = (size_t)s->h_blk_off[n];
+    s->scr_own_part = lay_out(partials, rows4 ? kProgPad : 1) > kNoAllocScratchBytes &&
+                      lay_out(partials, 1) > kNoAllocScratchBytes;
+    if (s->scr_own_part) lay_out(0, 1);
     s->start_iters.assign(n, 0);
   }
   *out = s;
@@ -1540,7 +1553,7 @@ int iterate_noalloc(pdvm_solver *s, int64_t max_iters, double tol, int32_t stop_
   const int n = s->n();
   for (int i = 0; i < n; ++i) s->start_iters[i] = s->host_ctl[i].iter;
   Scratch scr;
-  scr.part = (double *)(s->scratch_dev + s->scr_part);
+  scr.part = s->scr_own_part ? nullptr : (double *)(s->scratch_dev + s->scr_part);
   scr.progress = (int32_t *)(s->scratch_dev + s->scr_prog);
   scr.prog_pad = s->scr_pad;
   scr.xcc = (uint8_t *)(s->scratch_dev + s->scr_xcc);

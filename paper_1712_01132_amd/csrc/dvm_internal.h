@@ -208,7 +208,8 @@ constexpr int strip_nw(int shape) { return strip_g(shape) == 2 ? 4 : 8; }
 // records. A null member means each problem's own, in its workspace
 // (Geo::part, progress, xcc_seen). Otherwise it is one region for the whole
 // batch: problem p's partial sums at part + 4 blk_off[p], its counters and XCD
-// records at progress + row_off[p] and xcc + row_off[p].
+// records at progress + row_off[p] (prog_pad ints each with 4 x 4 tiles and stencil
+// rule 1) and xcc + row_off[p].
 struct Scratch {
   double *part = nullptr;
   int32_t *progress = nullptr;
