@@ -70,21 +70,19 @@ def timed_updates(solver, fluid, K, steps, warmup):
 # HBM bytes per sweep launch from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes
 # (scaled by a 1 GiB copy; summaries in profiles/), valid only for the kernel
 # source they were taken on. Key: (source hash, schedule, tile, bytes per value).
-_H = "3e9c9fb2dde38e62"
+_H = "f3b38972e25f7d2f"
 TRAFFIC = {
-    (_H, "rows-xcd", (4, 4), 8): 523.4e6 + 841.9e6,            # rock2d FP64
-    (_H, "rows-xcd", (4, 4), 4): 264.1e6 + 421.4e6,            # rock2d FP32
-    (_H, "queue", (4, 4, 4), 4): 12069.6e6 + 5104.0e6,         # pack3d FP32, 1 launch
-    (_H, "columns", (4, 4, 4), 4): 13454.6e6 + 5096.5e6,       # pack3d FP32, 1 launch
-    (_H, "queue", (8, 8), 4): 5960.5e6 + 4601.8e6,             # batch64 FP32, 1 launch
+    (_H, "rows-xcd", (4, 4), 8): 461.4e6 + 841.9e6,            # rock2d FP64
+    (_H, "rows-xcd", (4, 4), 4): 231.8e6 + 421.4e6,            # rock2d FP32
+    (_H, "queue", (4, 4, 4), 4): 6907.5e6 + 5104.0e6,         # pack3d FP32, 1 launch
+    (_H, "queue", (8, 8), 4): 4481.1e6 + 4601.8e6,             # batch64 FP32, 1 launch
 }
 # the same for the moment kernel of that iteration (h read once, moments written)
 MOM_TRAFFIC = {
     (_H, "rows-xcd", (4, 4), 8): 880.2e6 + 12.8e6,
-    (_H, "rows-xcd", (4, 4), 4): 445.3e6 + 9.5e6,
-    (_H, "queue", (4, 4, 4), 4): 5236.9e6 + 35.7e6,
-    (_H, "columns", (4, 4, 4), 4): 5236.9e6 + 35.7e6,
-    (_H, "queue", (8, 8), 4): 5821.9e6 + 184.4e6,
+    (_H, "rows-xcd", (4, 4), 4): 445.1e6 + 9.5e6,
+    (_H, "queue", (4, 4, 4), 4): 5236.2e6 + 35.7e6,
+    (_H, "queue", (8, 8), 4): 5823.3e6 + 184.4e6,
 }
 
 
@@ -116,7 +114,8 @@ def roofline(tm, elem, traffic_key=None, schedule="diagonals"):
     mom_traffic = MOM_TRAFFIC.get(traffic_key) if traffic_key else None
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-            "kernel": SWEEP_KERNEL.get(schedule, schedule),
+            "kernel": ("sweep_rows4_kernel" if schedule.startswith("rows") and traffic_key and max(traffic_key[2]) <= 4
+                       else SWEEP_KERNEL.get(schedule, schedule)),
             "bytes_per_launch": per_launch, "launch_ms": tm["sweep_ms_per_launch"],
             "launches_per_iter": tm["sweep_launches_per_iter"],
             "moments_kernel": {"bytes_per_launch": per_iter, "launch_ms": tm["moments_ms_per_launch"],
@@ -302,7 +301,7 @@ def unet_source_hash():
 
 # HBM bytes of one training step's MFMA kernels (FETCH_SIZE / WRITE_SIZE,
 # scaled; profiles/unet_train_bf16.md), by network source hash
-UNET_TRAFFIC = {"ddf9230b001a6b44": 5477.1e6 + 1223.3e6}
+UNET_TRAFFIC = {"7150255211ad138e": 3172.2e6 + 873.5e6}
 
 
 def unet_timing():
