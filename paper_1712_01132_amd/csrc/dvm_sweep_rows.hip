@@ -21,6 +21,9 @@ namespace {
 // * across bands they are read from h once the band below has published its
 //   progress counter. Stamps (seq * ntile0 + a + 1) never repeat, since seq
 //   advances with every arm and every reduction, so counters are never reset.
+//   With tiles one voxel high the second row is that of the wavefront below the
+//   band's top one, which therefore drains its stores into the L2 before it
+//   hands a tile on: the top one publishes the tile after taking it over.
 // Producers have lower block indices than their consumers (block = row_off[p]
 // + b * stride + c), so in-order dispatch cannot deadlock. Every wait is
 // bounded in wall-clock time (Geo::wait_ticks): one that exceeds it flags
@@ -163,6 +166,7 @@ __global__ void __launch_bounds__(kWave * NW)
   const bool gwait = w == 0 && band > 0;             // from the band below (h)
   const bool lmake = w < NW - 1 && j + 1 < ntile1;   // top rows to the wavefront above (LDS)
   const bool gmake = w == NW - 1 && j + 1 < ntile1;  // progress to the band above
+  const bool second = tile1 == 1 && lmake && w == NW - 2;  // the band above reads this row too
   const gptr<int32_t> wait_on = progress + (band > 0 ? (band - 1) * nchains + c : 0);
   const gptr<int32_t> publish = progress + band * nchains + c;
   const gptr<T> hz = hc;  // plane 0 of the current sweep
@@ -479,6 +483,7 @@ __global__ void __launch_bounds__(kWave * NW)
         ring[w][slot][k][lane] = res.T1[k];
         ring[w][slot][TT + k][lane] = T2[k];
       }
+      if (second) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       lds_post(&made[w], a + 1);
     }
     if (gmake) {

@@ -261,6 +261,8 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   const int ys = ys_of(j, cnt1);
   const bool lmake = w < NW - 1 && j + 1 < ntile1;   // top rows to the wavefront above (LDS)
   const bool gmake = w == NW - 1 && j + 1 < ntile1;  // progress to the band above
+  // tiles one voxel high: the band above reads the rows of the top two wavefronts
+  const bool thin = tile1 == 1, second = thin && lmake && w == NW - 2;
   const gptr<int32_t> publish = progress + (band * nchains + c) * pad;
   // one resource per voxel row (below 1 GiB, checked by the host); rows past a
   // ragged tile repeat its last one and store nothing
@@ -380,17 +382,22 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   // are counted from its own loads and stores alone
   __builtin_amdgcn_s_waitcnt(0);
 
+  // by one lane, when the stores of tiles below a are in the L2; the release of the
+  // agent-scope protocol also writes back what other wavefronts of the block stored
+  auto post_progress = [&](int a) __attribute__((always_inline)) {
+    __hip_atomic_store(publish, (int32_t)(seq * (uint32_t)ntile0 + (uint32_t)a),
+                       LOCAL ? __ATOMIC_RELAXED : __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  };
   for (int a = 0; a < ntile0; ++a) {
     int cnt0;
     const int xs = xs_of(a, cnt0);
     auto publish_last = [&]() __attribute__((always_inline)) {
-      if (!LOCAL || !gmake || a == 0) return;
+      if (a == 0 || !(second || (gmake && (LOCAL || thin)))) return;
       // tile a - 1's stores were followed by the loads of a record (four at
       // least): with at most four operations outstanding they are in the L2
       asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-      if (lane == 0)
-        __hip_atomic_store(publish, (int32_t)(seq * (uint32_t)ntile0 + (uint32_t)a), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+      if (second) return;  // the hand-over of tile a says so
+      if (lane == 0) post_progress(a);
     };
     T N[NC], B1[TT];
     const int32_t room = lmake ? lds_get(&used[w + 1]) : 0;  // looked at after the walk
@@ -568,16 +575,17 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
     }
     // --- the next tile's records, and the data of the one after it ------------------
     build(nxt, min(a + 1, ntile0 - 1));
-    if (!LOCAL && gmake && lane == 0)
-      __hip_atomic_store(publish, (int32_t)(seq * (uint32_t)ntile0 + (uint32_t)(a + 1)), __ATOMIC_RELEASE,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    if (!LOCAL && gmake && !thin && lane == 0) post_progress(a + 1);
     fetch(min(a + 2, ntile0 - 1), nxt);
   }
-  if (LOCAL && gmake) {
+  if (second || (gmake && (LOCAL || thin))) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane == 0)
-      __hip_atomic_store(publish, (int32_t)(seq * (uint32_t)ntile0 + (uint32_t)ntile0), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    if (second) {
+      lds_post(&made[w + 1], ntile0 + 1);
+    } else {
+      if (thin) lds_wait(&made[w], ntile0 + 1);
+      if (lane == 0) post_progress(ntile0);
+    }
   }
 }
 
