@@ -261,6 +261,19 @@ uint64_t fnv1a(uint64_t h, const void *data, size_t n) {
 // Blocks of the moment kernel at 16 fluid voxels per wavefront.
 int64_t moment_blocks16(int64_t fluid) { return std::max<int64_t>(1, std::min<int64_t>((fluid + 63) / 64, 1024)); }
 
+// Where a batch has more than kMomFoldFrom logical blocks of the moment kernel
+// (two rounds of the chip), one block does as many of them as make 16 voxels per
+// wavefront again; the sums stay those of the logical blocks. Moments per iteration,
+// a block each against folded: 8 problems of 32 - 64 a side, 16 x 16 velocities, FP32 (1000
+// logical blocks) 17 against 29 us; 24 of 64 - 200 (6000) 163 and 164; 64 of
+// 64 - 128, 24 x 24 velocities (16000) 293 against 269; 256 of 32 - 64, 8 x 8 velocities
+// (35000) 210 against 152 (with 16 voxels per wavefront from the outset 25, 163, 243, 137).
+constexpr int64_t kMomFoldFrom = 2048;
+int moment_fold(const Problem &P) {
+  const int64_t nw = (int64_t)P.mom_blocks * (kMomBlock / kWave), per = (P.fluid + nw - 1) / nw;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(16 / std::max<int64_t>(per, 1), kMomFoldMax));
+}
+
 int validate_and_build(const pdvm_config *cfg, Problem &P, std::string &err) {
   if (!cfg) { err = "config is NULL"; return PDVM_E_INVAL; }
   if (cfg->dim != 2 && cfg->dim != 3) { err = "dim must be 2 or 3"; return PDVM_E_INVAL; }
@@ -661,6 +674,7 @@ struct pdvm_solver {
   char *meta = nullptr;            // device: descriptors, offset tables, gathered control blocks
   Ctl *d_ctl_all = nullptr;
   std::vector<int> h_item_off, h_blk_off, h_row_off, h_strip_off;
+  int64_t mom_partials = 0;  // logical blocks of the moment kernel, all problems
   Batch<double> bd;
   Batch<float> bf;
   Ctl *host_ctl = nullptr;         // pinned, one per problem
@@ -846,7 +860,16 @@ int finalize_batch(pdvm_solver *s) {
     s->h_item_off[(size_t)d * (n + 1) + n] = acc;
   }
   s->h_blk_off.assign(n + 1, 0);
-  for (int p = 0; p < n; ++p) s->h_blk_off[p + 1] = s->h_blk_off[p] + s->P[p].mom_blocks;
+  s->mom_partials = 0;
+  for (int p = 0; p < n; ++p) s->mom_partials += s->P[p].mom_blocks;
+  const bool fold = s->mom_partials > kMomFoldFrom;
+  for (int p = 0, off = 0; p < n; ++p) {
+    Geo<T> &g = geos<T>(s)[p];
+    g.mom_fold = fold ? moment_fold(s->P[p]) : 1;
+    g.part_off = off;
+    off += s->P[p].mom_blocks;
+    s->h_blk_off[p + 1] = s->h_blk_off[p] + (s->P[p].mom_blocks + g.mom_fold - 1) / g.mom_fold;
+  }
   int tile_edge = kTileEdge[0];
   for (auto &P : s->P)
     if (std::max(P.tile[0], P.tile[1]) > kTileEdge[0]) tile_edge = kTileEdge[1];
@@ -897,6 +920,7 @@ int finalize_batch(pdvm_solver *s) {
   B.d_geo = (const Geo<T> *)geo;
   B.d_item_off = (const int *)item;
   B.d_blk_off = (const int *)blk;
+  B.mom_folded = fold;
   B.h_item_off = s->h_item_off.data();
   B.h_blk_off = s->h_blk_off.data();
   B.d_row_off = (const int *)rowo;
@@ -1436,7 +1460,7 @@ int create_common(const pdvm_config *cfgs, int n, void *dev_workspace, size_t ws
     size_t partials16 = 0;
     for (const Problem &P : s->P) partials16 += (size_t)moment_blocks16(P.fluid);
     s->scr_need = lay_out(partials16, 1);
-    const size_t partials = (size_t)s->h_blk_off[n];
+    const size_t partials = (size_t)s->mom_partials;
     s->scr_own_part = lay_out(partials, rows4 ? kProgPad : 1) > kNoAllocScratchBytes &&
                       lay_out(partials, 1) > kNoAllocScratchBytes;
     if (s->scr_own_part) lay_out(0, 1);

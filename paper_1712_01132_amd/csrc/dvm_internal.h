@@ -15,6 +15,7 @@ constexpr int band_waves(int tile_edge) { return tile_edge == 4 ? 8 : 4; }
 constexpr int kProgPad = 32;
 constexpr int kRing = 64;     // permeability history kept at multiples of 100 iterations
 constexpr int kMomBlock = 256;
+constexpr int kMomFoldMax = 8;
 constexpr int kSrcStride = 4; // per-voxel source record: nu rho, 2 nu u_1, 2 nu u_2, 2 nu u_3 (0 in 2D)
 
 // Per-voxel flags, computed once on the host from the solid mask (the paper's
@@ -97,7 +98,9 @@ struct Geo {
   double *u[2];            // [3][N]
   Ctl *ctl;
   double *part;            // [mom_blocks][4] per-block residual / flux partials
-  int32_t mom_blocks;
+  int32_t mom_blocks;      // logical blocks of the moment kernel
+  int32_t mom_fold = 1;    // logical blocks per block
+  int32_t part_off = 0;    // first logical block's partials in a scratch region
   const int32_t *fluid_idx;  // [nfluid] the fluid voxels in index order (moment kernel's work list)
   int64_t nfluid;
   int32_t tile[3], ntile[3];
@@ -151,6 +154,7 @@ struct Batch {
   const Geo<T> *d_geo = nullptr;
   const int *d_item_off = nullptr;   // [ndiag_max][nprob + 1] sweep blocks per diagonal
   const int *d_blk_off = nullptr;    // [nprob + 1] moment-kernel blocks
+  int mom_folded = 0;                // some problem's mom_fold is not 1
   const int *h_item_off = nullptr;   // host copies
   const int *h_blk_off = nullptr;
   // row-pipeline sweep: problem p owns blocks [row_off[p], row_off[p + 1]),
@@ -207,7 +211,7 @@ constexpr int strip_nw(int shape) { return strip_g(shape) == 2 ? 4 : 8; }
 // partial sums, the row pipeline's progress counters and per-block XCD
 // records. A null member means each problem's own, in its workspace
 // (Geo::part, progress, xcc_seen). Otherwise it is one region for the whole
-// batch: problem p's partial sums at part + 4 blk_off[p], its counters and XCD
+// batch: problem p's partial sums at part + 4 Geo::part_off, its counters and XCD
 // records at progress + row_off[p] (prog_pad ints each with 4 x 4 tiles and stencil
 // rule 1) and xcc + row_off[p].
 struct Scratch {

@@ -66,6 +66,9 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
 // distribution is loaded before the current one is reduced, so a wavefront
 // always has a voxel's loads in flight. Slots past the octant size read a
 // valid neighbour (same cache lines) and weigh 0.
+// FOLD: a block does the work of Geo::mom_fold logical blocks, one after the
+// other, so that a batch with more blocks than it needs has fewer while each
+// problem's partial sums are the ones it has alone.
 template <typename T>
 using vec2_t = T __attribute__((ext_vector_type(2)));
 
@@ -79,7 +82,7 @@ using vec2_t = T __attribute__((ext_vector_type(2)));
 // the slots q = (l & 31) + 32 m of its half's voxel), for octant sizes just
 // above a multiple of 64 (144 velocities per octant: 160 slots per voxel
 // instead of 192, and half the reductions and result stores per voxel).
-template <typename T, int DIM, int NS, bool PAIR, bool SH, bool HALF = false>
+template <typename T, int DIM, int NS, bool PAIR, bool SH, bool HALF, bool FOLD>
 __global__ void __launch_bounds__(kMomBlock)
     moments_kernel(const Geo<T> *__restrict__ G, const int *__restrict__ blk_off, int nprob, double *part_scr) {
   static_assert(!(HALF && PAIR), "one slot layout at a time");
@@ -99,9 +102,9 @@ __global__ void __launch_bounds__(kMomBlock)
   const gptr<T> wall_n = as_global(np ? g.wall[1] : g.wall[0]);
   const gptr<const int32_t> fidx = as_global(g.fluid_idx);
   const gptr<const double> wq = as_global(g.wq);
-  const gptr<double> part = as_global(part_scr ? part_scr + 4 * (int64_t)(nprob > 1 ? blk_off[pb] : 0) : g.part);
+  const gptr<double> part = as_global(part_scr ? part_scr + 4 * (int64_t)g.part_off : g.part);
   const int64_t N = g.N, Kpad = g.Kpad, nf = g.nfluid;
-  const int Ko = g.Ko, Ko_pad = g.Ko_pad, tau_fb = g.tau_fb, mom_blocks = g.mom_blocks;
+  const int Ko = g.Ko, Ko_pad = g.Ko_pad, tau_fb = g.tau_fb, mom_blocks = g.mom_blocks, fold = FOLD ? g.mom_fold : 1;
   const double nu = g.nu, Dj[3] = {g.D[0], g.D[1], g.D[2]};
   const int dev = g.dev;
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
@@ -142,27 +145,65 @@ __global__ void __launch_bounds__(kMomBlock)
   };
   // the next voxel's distribution is held in registers only when it is small
   constexpr bool kAhead = (1 << DIM) * NS * sizeof(T) <= 256;
+  __shared__ double sh[WPB][2], sums[FOLD ? kMomFoldMax : 1][WPB];
   double mdu = 0, mu = 0, su = 0;
-  const int64_t first = (int64_t)blk * WPB + wid;
-  for (int64_t base = first; base < nf; base += nw * kWave) {
-    // this wavefront's next (up to) 64 voxels: lane t holds the index of voxel base + t nw
-    const int64_t il = base + (int64_t)lane * nw;
-    const int32_t cl = fidx[il < nf ? il : base];
-    const int cnt = (int)min<int64_t>(kWave, (nf - base + nw - 1) / nw);
-    // HALF: step t takes voxels 2 t (lanes 0-31) and 2 t + 1 (lanes 32-63;
-    // none past an odd count: that half re-reads the last one and stores nothing)
+  if (FOLD && lane < fold) sums[lane][wid] = 0;
+  // the sum of logical block f ends
+  auto end_sum = [&](int f) __attribute__((always_inline)) {
+    if (HALF) su += __shfl_xor(su, 32, kWave);  // lane 32's voxels into lane 0's accumulator
+    if (lane == 0) sums[f][wid] = su;
+    su = 0;
+  };
+  // a logical block's wavefront has at most `per` voxels where blocks are folded
+  // (the host folds only as many as 64 lanes list)
+  const int per = FOLD && fold > 1 ? (int)((nf + nw - 1) / nw) : kWave;
+  const int lf = FOLD && fold > 1 ? lane / per : 0, lt = lane - lf * per;
+  int fs = 0;  // the logical block of the current sum
+  for (int64_t base = (int64_t)blk * fold * WPB + wid; base < nf; base += nw * kWave) {
+    // this wavefront's next (up to) 64 voxels: lane t holds the index of voxel base + t nw, folded: of
+    // voxel t % per of logical block t / per
+    const int64_t il = base + lf * WPB + (int64_t)lt * nw;
+    const bool mine = il < nf && (!FOLD || (lf < fold && blk * fold + lf < mom_blocks));
+    const int32_t cl = fidx[mine ? il : base];
+    uint64_t left = __ballot(mine);
+    // HALF: a step takes two voxels of a logical block (lanes 0-31 and 32-63; none past
+    // an odd count: that half re-reads the first and stores nothing)
     const int hsel = HALF ? lane >> 5 : 0;
-    auto voxel = [&](int t) __attribute__((always_inline)) {
-      if (!HALF) return (int64_t)__builtin_amdgcn_readlane(cl, t);
-      const int32_t a = __builtin_amdgcn_readlane(cl, 2 * t), b = __builtin_amdgcn_readlane(cl, min(2 * t + 1, cnt - 1));
+    // the lanes listing the next step's voxels
+    int t0, t1;
+    auto take = [&]() __attribute__((always_inline)) {
+      t0 = t1 = __builtin_ctzll(left);
+      left &= left - 1;
+      if (HALF && left) {
+        const int t = __builtin_ctzll(left);
+        if (!FOLD || __builtin_amdgcn_readlane(lf, t) == __builtin_amdgcn_readlane(lf, t0)) {
+          t1 = t;
+          left &= left - 1;
+        }
+      }
+    };
+    auto voxel = [&]() __attribute__((always_inline)) {
+      const int32_t a = __builtin_amdgcn_readlane(cl, t0);
+      if (!HALF) return (int64_t)a;
+      const int32_t b = __builtin_amdgcn_readlane(cl, t1);
       return (int64_t)(hsel ? b : a);
     };
-    const int steps = HALF ? (cnt + 1) / 2 : cnt;
     T hv[1 << DIM][NS];
-    int64_t c = voxel(0);
+    take();
+    int64_t c = voxel();
     load(c, hv);
-    for (int t = 0; t < steps; ++t) {
-      const int64_t cn = voxel(min(t + 1, steps - 1));
+    for (int steps_left = 1; steps_left;) {
+      const bool two = t1 != t0;
+      if constexpr (FOLD) {
+        const int f = __builtin_amdgcn_readlane(lf, t0);
+        if (f != fs) {
+          end_sum(fs);
+          fs = f;
+        }
+      }
+      steps_left = left != 0;
+      if (steps_left) take();
+      const int64_t cn = voxel();
       T hn[1 << DIM][NS];
       if (kAhead) load(cn, hn);  // in flight while this voxel is reduced
       double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // rho, half-fluxes (j, +/-), energy
@@ -214,7 +255,7 @@ __global__ void __launch_bounds__(kMomBlock)
         if (SH) qf[j] = DIM == 2 ? total(tot, 5 + j) : total(qt, j);
       }
       const double en = total(tot, 7);
-      if ((lane & (LW - 1)) == 0 && (!HALF || 2 * t + hsel < cnt)) {
+      if ((lane & (LW - 1)) == 0 && (!HALF || !hsel || two)) {
         // Offset form: the sums above are moments of h - rho_r. rho_r adds
         // rho_r w0 to rho, rho_r D_j to each half-flux (so nothing to u) and
         // rho_r we to the energy. The records then describe the sweep of
@@ -255,28 +296,27 @@ __global__ void __launch_bounds__(kMomBlock)
       c = cn;
     }
   }
+  end_sum(fs);
   if (HALF) {  // lane 32's voxels into lane 0's accumulators
     mdu = fmax(mdu, __shfl_xor(mdu, 32, kWave));
     mu = fmax(mu, __shfl_xor(mu, 32, kWave));
-    su += __shfl_xor(su, 32, kWave);
   }
-  __shared__ double sh[WPB][3];
   if (lane == 0) {
     sh[wid][0] = mdu;
     sh[wid][1] = mu;
-    sh[wid][2] = su;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  const int lb = blk * fold + threadIdx.x;  // a thread per logical block; the maxima are the block's
+  if (threadIdx.x < fold && lb < mom_blocks) {
     double a = 0, b = 0, cc = 0;
     for (int w = 0; w < WPB; ++w) {
       a = fmax(a, sh[w][0]);
       b = fmax(b, sh[w][1]);
-      cc += sh[w][2];
+      cc += sums[threadIdx.x][w];
     }
-    part[blk * 4 + 0] = a;
-    part[blk * 4 + 1] = b;
-    part[blk * 4 + 2] = cc;
+    part[lb * 4 + 0] = a;
+    part[lb * 4 + 1] = b;
+    part[lb * 4 + 2] = cc;
   }
 }
 
@@ -296,12 +336,11 @@ __device__ void resolve(Geo<T> &g, int par, int run) {
 
 template <typename T>
 __global__ void __launch_bounds__(256)
-    reduce_kernel(Geo<T> *__restrict__ G, const int *__restrict__ blk_off, const int *__restrict__ row_off,
-                  double *part_scr, uint8_t *xcc_scr, const int32_t *qctr, int q_total) {
+    reduce_kernel(Geo<T> *__restrict__ G, const int *__restrict__ row_off, double *part_scr, uint8_t *xcc_scr, const int32_t *qctr, int q_total) {
   Geo<T> &g = G[blockIdx.x];
   Ctl *ctl = g.ctl;
   if (ctl->stop) return;
-  const double *part = part_scr ? part_scr + 4 * (int64_t)blk_off[blockIdx.x] : g.part;
+  const double *part = part_scr ? part_scr + 4 * (int64_t)g.part_off : g.part;
   const uint8_t *xcc_seen = g.xcc_seen && xcc_scr ? xcc_scr + row_off[blockIdx.x] : g.xcc_seen;  // row_off: the pipeline's block offsets
   const int nblocks = g.mom_blocks;
   const int64_t N = g.N;
@@ -607,12 +646,17 @@ int grid_for(int64_t work, int block) {
 
 template <typename T, int D, int S, bool P, bool H = false>
 void launch_moments_as(const Batch<T> &B, int blocks, hipStream_t st, double *part) {
-  if (B.shakhov)
-    hipLaunchKernelGGL((moments_kernel<T, D, S, P, true, H>), dim3(blocks), dim3(kMomBlock), 0, st, B.d_geo,
-                       B.d_blk_off, B.nprob, part);
-  else
-    hipLaunchKernelGGL((moments_kernel<T, D, S, P, false, H>), dim3(blocks), dim3(kMomBlock), 0, st, B.d_geo,
-                       B.d_blk_off, B.nprob, part);
+#define PDVM_MOM_AS(SHV, F)                                                                          \
+  hipLaunchKernelGGL((moments_kernel<T, D, S, P, SHV, H, F>), dim3(blocks), dim3(kMomBlock), 0, st, B.d_geo, \
+                     B.d_blk_off, B.nprob, part)
+  if (B.mom_folded) {
+    if (B.shakhov) PDVM_MOM_AS(true, true);
+    else PDVM_MOM_AS(false, true);
+  } else {
+    if (B.shakhov) PDVM_MOM_AS(true, false);
+    else PDVM_MOM_AS(false, false);
+  }
+#undef PDVM_MOM_AS
 }
 
 template <typename T>
@@ -674,7 +718,7 @@ hipError_t launch_moments(const Batch<T> &B, hipStream_t st, const Scratch &scr)
 template <typename T>
 hipError_t launch_reduce(const Batch<T> &B, hipStream_t st, const Scratch &scr) {
   const int32_t *qctr = B.use_queue ? (scr.qctr ? scr.qctr : B.d_qctr) : nullptr;
-  hipLaunchKernelGGL((reduce_kernel<T>), dim3(B.nprob), dim3(256), 0, st, const_cast<Geo<T> *>(B.d_geo), B.d_blk_off,
+  hipLaunchKernelGGL((reduce_kernel<T>), dim3(B.nprob), dim3(256), 0, st, const_cast<Geo<T> *>(B.d_geo),
                      B.use_strips ? B.d_strip_off : B.d_row_off, scr.part, scr.xcc, qctr, B.q_total);
   return hipGetLastError();
 }
