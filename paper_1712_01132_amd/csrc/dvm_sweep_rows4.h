@@ -354,11 +354,13 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
     rdrop = fl ? 0u : kDrop;
     live = __ballot(fl) != 0 || cnt1 == 1;
     // a DPP operand may be read two instructions after its write at the earliest
-    asm volatile("s_nop 1" ::"v"(rs[0]), "v"(rs[1]), "v"(rs[2]), "v"(rc1[0]), "v"(rc1[1]), "v"(rc2[0]), "v"(rc2[1]),
-                 "v"(rw[0]), "v"(rw[1]), "v"(rdo), "v"(rdrop));
-    if (TAU) asm volatile("s_nop 1" ::"v"(rt));
-    if (SH) asm volatile("s_nop 1" ::"v"(rq[0]), "v"(rq[1]));
-    if (MW) asm volatile("s_nop 1" ::"v"(rm[0]), "v"(rm[1]));
+    // ("+v": the values are those of this point, not formed again after it)
+    asm volatile("s_nop 1"
+                 : "+v"(rs[0]), "+v"(rs[1]), "+v"(rs[2]), "+v"(rc1[0]), "+v"(rc1[1]), "+v"(rc2[0]), "+v"(rc2[1]),
+                   "+v"(rw[0]), "+v"(rw[1]), "+v"(rdo), "+v"(rdrop));
+    if (TAU) asm volatile("s_nop 1" : "+v"(rt));
+    if (SH) asm volatile("s_nop 1" : "+v"(rq[0]), "+v"(rq[1]));
+    if (MW) asm volatile("s_nop 1" : "+v"(rm[0]), "+v"(rm[1]));
   };
   T L1[TT], L2[TT];  // left halo: previous tile's last two columns, or images across the x1 wrap
 #pragma unroll
@@ -382,6 +384,10 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   // are counted from its own loads and stores alone
   __builtin_amdgcn_s_waitcnt(0);
 
+  // the fewest loads that `fetch` can become: the flags, the sources (one, if they
+  // are merged) and two wall values, all from addresses of their own. The fence before
+  // the loop's fetch and the one in the wait keep them between the stores and it.
+  constexpr int kRecordLoads = 4;
   // by one lane, when the stores of tiles below a are in the L2; the release of the
   // agent-scope protocol also writes back what other wavefronts of the block stored
   auto post_progress = [&](int a) __attribute__((always_inline)) {
@@ -393,9 +399,9 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
     const int xs = xs_of(a, cnt0);
     auto publish_last = [&]() __attribute__((always_inline)) {
       if (a == 0 || !(second || (gmake && (LOCAL || thin)))) return;
-      // tile a - 1's stores were followed by the loads of a record (four at
-      // least): with at most four operations outstanding they are in the L2
-      asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      // tile a - 1's stores were followed by the loads of a record: with at most
+      // as many operations outstanding they are in the L2
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kRecordLoads) : "memory");
       if (second) return;  // the hand-over of tile a says so
       if (lane == 0) post_progress(a);
     };
@@ -576,6 +582,7 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
     // --- the next tile's records, and the data of the one after it ------------------
     build(nxt, min(a + 1, ntile0 - 1));
     if (!LOCAL && gmake && !thin && lane == 0) post_progress(a + 1);
+    asm volatile("" ::: "memory");
     fetch(min(a + 2, ntile0 - 1), nxt);
   }
   if (second || (gmake && (LOCAL || thin))) {
