@@ -61,7 +61,10 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   constexpr int DIM = 2, TT = 4, NC = 16;
   constexpr int RING = 2, RING_IN = 4;  // slots of each hand-over: from the row below, from the importer
   constexpr bool TAU = (EXT & 1) != 0, SH = (EXT & 2) != 0, MW = (EXT & 4) != 0;
-  constexpr uint32_t kDrop = 0x40000000u;  // past any row's range; a sum of two does not wrap
+  // 8 MiB past any row's range (1 GiB), so also from columns that a ragged or narrow
+  // tile does not have, up to three voxels of 32 KiB before the row's start; the bits
+  // of 4.0f, an inline constant (a literal costs the FP32 sweeps 1 %)
+  constexpr uint32_t kDrop = 0x40800000u;
   __shared__ T rd_lds[4 * kWave];
   // wavefront w reads its bottom halo from slot a of ring_of(w)
   __shared__ T ring[(NW - 1) * RING + RING_IN][2 * TT][kWave];
