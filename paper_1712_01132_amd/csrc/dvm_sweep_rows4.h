@@ -54,6 +54,14 @@ namespace {
 // 64^2 cell with 16 x 16 velocities FP64 70 -> 49 us, 203 x 157 with 16 x 16
 // velocities, tau, Shakhov and Maxwell walls FP64 414 -> 242 us (one branch and one
 // load after the other per voxel at a wall, against one round trip per axis of a tile).
+//
+// The counter of a band and chain, `pad` ints each (more than 2^31 ints for the tallest
+// problems that fit the memory: 280 M one-voxel rows, four chains).
+__host__ __device__ constexpr int64_t counter_at(int band, int nchains, int c, int pad) {
+  return ((int64_t)band * nchains + c) * pad;
+}
+static_assert(counter_at(35000000, 4, 3, kProgPad) == 4480000096ll, "counter offsets are 64-bit");
+
 template <typename T, bool LOCAL, int NW, int EXT>
 __global__ void __launch_bounds__(kWave * (NW + 1))
     sweep_rows4_kernel(const Geo<T> *__restrict__ G, const int *__restrict__ row_off, int nprob, int stride,
@@ -200,7 +208,7 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   if (w == NW) {  // the importer
     int cnt1;
     const int ys = ys_of(band * NW, cnt1);
-    const gptr<int32_t> wait_on = progress + (band > 0 ? ((band - 1) * nchains + c) * pad : 0);
+    const gptr<int32_t> wait_on = progress + (band > 0 ? counter_at(band - 1, nchains, c, pad) : 0);
     const uint32_t base = seq * (uint32_t)ntile0;
     // the band below's progress in tiles: the last seen, and a look at it that
     // is in flight with a tile's loads, so that a tile takes one round trip
@@ -266,7 +274,7 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
   const bool gmake = w == NW - 1 && j + 1 < ntile1;  // progress to the band above
   // tiles one voxel high: the band above reads the rows of the top two wavefronts
   const bool thin = tile1 == 1, second = thin && lmake && w == NW - 2;
-  const gptr<int32_t> publish = progress + (band * nchains + c) * pad;
+  const gptr<int32_t> publish = progress + counter_at(band, nchains, c, pad);
   // one resource per voxel row (below 1 GiB, checked by the host); rows past a
   // ragged tile repeat its last one and store nothing
   __amdgpu_buffer_rsrc_t rowrs[TT];
