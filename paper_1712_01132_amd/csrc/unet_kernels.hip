@@ -756,7 +756,7 @@ hipError_t conv_as(ConvArgs a, hipStream_t st) {
 
 hipError_t launch_conv(const ConvArgs &a, hipStream_t st) {
   const int Cin = a.Ca + a.Cb;
-  if (a.taps == 1) return a.nrows % 64 == 0 ? conv_as<2, 2, 1, false>(a, st) : conv_as<4, 1, 1, false>(a, st);
+  if (a.taps == 1) return conv_as<4, 1, 1, false>(a, st);  // the head: 32 rows either way
   if (Cin == 8) return conv_as<4, 1, 9, true>(a, st);
   // 128 output channels of 64 pixels, 64 of 128, 32 of 256: the fewest wavefronts read the same weights or pixels
   if (a.nrows % 128 == 0) return conv_as<1, 4, 9, false>(a, st);
@@ -792,8 +792,7 @@ hipError_t launch_wgrad(WgradArgs a, hipStream_t st) {
   else                                                                                              \
     wgrad_as<T, M, C, (386 * 2 + 64 * M - 1) / (64 * M)>(a, st)
   if (a.taps == 1) {
-    if (c32) { PDVM_WG(1, 1, 2); }
-    else { PDVM_WG(1, 1, 1); }
+    PDVM_WG(1, 1, 2);  // the head: 32 input channels
   } else if (!c32) {
     PDVM_WG(3, 1, 1);
   } else if (wide) {
