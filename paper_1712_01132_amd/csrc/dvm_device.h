@@ -39,9 +39,10 @@ __device__ __forceinline__ gptr<T> as_global(T *p) {
   return (gptr<T>)p;
 }
 
-// Raw buffer stores (the 2D row pipeline): one resource per tile, the
-// voxel's byte offset as a scalar and the lane's slot as a vector offset.
-// Range checking is off in effect (the record count is the maximum).
+// Raw buffer accesses. The tile sweep, the 4 x 4 row pipeline and the strips take
+// one resource per voxel row and rely on its range check: a store or load at an
+// offset past the row is dropped (a load gives 0). sweep_rows_kernel stores through
+// one resource per tile with the largest record count, so there nothing is checked.
 constexpr int kBufferFlags = 0x00020000;  // 32-bit data format, as untyped buffer accesses need
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void buffer_store(double v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {

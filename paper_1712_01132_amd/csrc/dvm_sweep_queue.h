@@ -34,7 +34,11 @@ namespace {
 // the segment's start).
 // Occupancy (FP32): 4 wavefronts per SIMD in 2D (the 64-problem batch sweeps in
 // 2.21 ms instead of 2.29 with 3), 3 in 3D (at 4 the 4x4 tile spills its x3
-// planes: 5.8 ms on the 96^3 pack instead of 4.3).
+// planes: 5.8 ms on the 96^3 pack instead of 4.3, measured with records in LDS). At 3
+// (168 VGPRs) tile items of 4x4 with stencil rule 1 do not spill (Maxwell walls with
+// Shakhov: one register); with rule 0 10 - 13 registers, columns 3 - 37, and 8x8 tiles
+// 48 - 90 (per-diagonal launches of those, without the bound, spill none: 48 x 44 x 40 with
+// 16^3 velocities 1.00 ms a sweep against 1.21 from the queue).
 template <typename T, int DIM, int TT, bool Y2WALL, int EXT, bool COL>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (DIM == 2 ? 4 : 3) : 1)))
     sweep_queue_kernel(const Geo<T> *__restrict__ G, const uint64_t *__restrict__ items,

@@ -49,10 +49,10 @@ namespace {
 // two wavefronts to a SIMD (1.6 us per tile; one alone takes 1.2), and the 0.7
 // us from a row to the next one above.
 // Measured (MI355X, sweep per iteration, this kernel against sweep_rows_kernel
-// with 4 x 4 tiles): 512^2 rock with 32 x 32 velocities FP64 0.66 -> 0.44 ms,
-// FP32 0.53 -> 0.31 ms; 540^2 image with 8 x 8 velocities FP64 0.66 -> 0.40 ms;
-// 64^2 cell with 16 x 16 velocities FP64 70 -> 49 us, 203 x 157 with 16 x 16
-// velocities, tau, Shakhov and Maxwell walls FP64 414 -> 242 us (one branch and one
+// with 4 x 4 tiles): 512^2 rock with 32 x 32 velocities FP64 664 -> 418 us,
+// FP32 533 -> 322 us; 540^2 image with 8 x 8 velocities FP64 612 -> 406 us;
+// 64^2 cell with 16 x 16 velocities FP64 73 -> 52 us, 203 x 157 with 16 x 16
+// velocities, tau, Shakhov and Maxwell walls FP64 421 -> 233 us (one branch and one
 // load after the other per voxel at a wall, against one round trip per axis of a tile).
 //
 // The counter of a band and chain, `pad` ints each (more than 2^31 ints for the tallest
@@ -210,8 +210,9 @@ __global__ void __launch_bounds__(kWave * (NW + 1))
     const int ys = ys_of(band * NW, cnt1);
     const gptr<int32_t> wait_on = progress + (band > 0 ? counter_at(band - 1, nchains, c, pad) : 0);
     const uint32_t base = seq * (uint32_t)ntile0;
-    // the band below's progress in tiles: the last seen, and a look at it that
-    // is in flight with a tile's loads, so that a tile takes one round trip
+    // the band below's progress in tiles, as last seen: a look at it before each
+    // tile's loads (LOCAL) mostly saves the next tile its poll. The look is waited for
+    // before the loads are issued (`base` is subtracted at once): two round trips a tile
     auto look = [&]() __attribute__((always_inline)) {
       return (int32_t)((uint32_t)__hip_atomic_load(wait_on, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base);
     };
