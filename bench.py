@@ -70,19 +70,19 @@ def timed_updates(solver, fluid, K, steps, warmup):
 # HBM bytes per sweep launch from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes
 # (scaled by a 1 GiB copy; summaries in profiles/), valid only for the kernel
 # source they were taken on. Key: (source hash, schedule, tile, bytes per value).
-_H = "f3b38972e25f7d2f"
+_H = "f3b615f216264a97"
 TRAFFIC = {
     (_H, "rows-xcd", (4, 4), 8): 461.4e6 + 841.9e6,            # rock2d FP64
-    (_H, "rows-xcd", (4, 4), 4): 231.8e6 + 421.4e6,            # rock2d FP32
-    (_H, "queue", (4, 4, 4), 4): 6907.5e6 + 5104.0e6,         # pack3d FP32, 1 launch
-    (_H, "queue", (8, 8), 4): 4481.1e6 + 4601.8e6,             # batch64 FP32, 1 launch
+    (_H, "rows-xcd", (4, 4), 4): 231.6e6 + 421.4e6,            # rock2d FP32
+    (_H, "queue", (4, 4, 4), 4): 6909.6e6 + 5104.0e6,         # pack3d FP32, 1 launch
+    (_H, "queue", (8, 8), 4): 4477.8e6 + 4601.8e6,             # batch64 FP32, 1 launch
 }
 # the same for the moment kernel of that iteration (h read once, moments written)
 MOM_TRAFFIC = {
     (_H, "rows-xcd", (4, 4), 8): 880.2e6 + 12.8e6,
     (_H, "rows-xcd", (4, 4), 4): 445.1e6 + 9.5e6,
     (_H, "queue", (4, 4, 4), 4): 5236.2e6 + 35.7e6,
-    (_H, "queue", (8, 8), 4): 5823.3e6 + 184.4e6,
+    (_H, "queue", (8, 8), 4): 5816.5e6 + 184.1e6,
 }
 
 
@@ -301,7 +301,7 @@ def unet_source_hash():
 
 # HBM bytes of one training step's MFMA kernels (FETCH_SIZE / WRITE_SIZE,
 # scaled; profiles/unet_train_bf16.md), by network source hash
-UNET_TRAFFIC = {"7150255211ad138e": 3172.2e6 + 873.5e6}
+UNET_TRAFFIC = {"653b2631c8fd6770": 3172.4e6 + 873.6e6}
 
 
 def unet_timing():
