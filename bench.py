@@ -70,7 +70,7 @@ def timed_updates(solver, fluid, K, steps, warmup):
 # HBM bytes per sweep launch from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes
 # (scaled by a 1 GiB copy; summaries in profiles/), valid only for the kernel
 # source they were taken on. Key: (source hash, schedule, tile, bytes per value).
-_H = "f3b615f216264a97"
+_H = "5815b882cdfb3b18"
 TRAFFIC = {
     (_H, "rows-xcd", (4, 4), 8): 461.4e6 + 841.9e6,            # rock2d FP64
     (_H, "rows-xcd", (4, 4), 4): 231.6e6 + 421.4e6,            # rock2d FP32

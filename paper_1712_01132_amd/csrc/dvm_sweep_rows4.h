@@ -7,6 +7,13 @@
 namespace pdvm {
 namespace {
 
+// The counter of a band and chain, `pad` ints each (more than 2^31 ints for the tallest
+// problems that fit the memory: 280 M one-voxel rows, four chains).
+__host__ __device__ constexpr int64_t counter_at(int band, int nchains, int c, int pad) {
+  return ((int64_t)band * nchains + c) * pad;
+}
+static_assert(counter_at(35000000, 4, 3, kProgPad) == 4480000096ll, "counter offsets are 64-bit");
+
 // The pipeline, its hand-overs, its waits and their protocols are those of
 // sweep_rows_kernel. What differs:
 //
@@ -54,14 +61,6 @@ namespace {
 // 64^2 cell with 16 x 16 velocities FP64 73 -> 52 us, 203 x 157 with 16 x 16
 // velocities, tau, Shakhov and Maxwell walls FP64 421 -> 233 us (one branch and one
 // load after the other per voxel at a wall, against one round trip per axis of a tile).
-//
-// The counter of a band and chain, `pad` ints each (more than 2^31 ints for the tallest
-// problems that fit the memory: 280 M one-voxel rows, four chains).
-__host__ __device__ constexpr int64_t counter_at(int band, int nchains, int c, int pad) {
-  return ((int64_t)band * nchains + c) * pad;
-}
-static_assert(counter_at(35000000, 4, 3, kProgPad) == 4480000096ll, "counter offsets are 64-bit");
-
 template <typename T, bool LOCAL, int NW, int EXT>
 __global__ void __launch_bounds__(kWave * (NW + 1))
     sweep_rows4_kernel(const Geo<T> *__restrict__ G, const int *__restrict__ row_off, int nprob, int stride,
